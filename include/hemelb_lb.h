@@ -126,8 +126,9 @@ typedef struct {
  *   flags        HEMELB_FLAG_*
  *   n_sites      N >= 0 fluid sites (N + ghost links must stay below 2^30)
  *   coords       int32 [N][3] site coordinates in [0, 2^21), or NULL.  When given,
- *                sites are processed in Morton (Z-order, x lowest bit) order and the
- *                wall normals can be derived; results still come back in caller order.
+ *                sites are processed block by block (4x4x4 blocks in Morton order, z lowest
+ *                bit; z fastest inside a block) and the wall normals can be derived;
+ *                results still come back in caller order.
  *   nbr          int32 [N][lattice]: nbr[s][i] = upstream code of direction i at
  *                site s: a site index (>= 0), HEMELB_LINK_WALL, or HEMELB_LINK_IOLET(k).
  *                Column 0 (rest) is ignored.  Fluid links must be reciprocal:
@@ -201,7 +202,7 @@ int hemelb_lb_links(const uint8_t* labels, const int32_t shape[3], const int32_t
                     int32_t lattice, int64_t* n_sites, int32_t* coords, int32_t* nbr);
 
 /*
- * Create a handle: validate (no device work on failure), Morton-order the sites,
+ * Create a handle: validate (no device work on failure), order the sites block by block,
  * build the device neighbour table, allocate ping-pong population buffers and
  * set the rest equilibrium at time 0.
  * Errors: EINVAL (message names the first offending site/direction), ENOMEM, EDEVICE.
@@ -212,8 +213,8 @@ int hemelb_lb_links(const uint8_t* labels, const int32_t shape[3], const int32_t
  *                          leaves the hardware's round-robin)
  *   HEMELB_STAGE_TILES=W   tiles per workgroup that copy their own populations into
  *                          LDS first: 4, 8 or 16, anything else none (default, with
- *                          block addressing: FP32 8 for D3Q15 from 4M sites, else 4;
- *                          none below 256 four-tile groups or with 16-bit storage)
+ *                          block addressing: 8 for FP32 D3Q15 from 1M sites, else 4;
+ *                          none below 256 four-tile groups)
  *   HEMELB_LDS_DMA=0       make that copy go through registers instead of loads
  *                          that write LDS directly
  *   HEMELB_VERBOSE=1       print the time of each setup phase to stderr

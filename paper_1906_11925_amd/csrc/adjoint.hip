@@ -178,12 +178,12 @@ __global__ __launch_bounds__(64) void k_objective_final(const double* __restrict
 // ---------------------------------------------------------------------------
 // Adds to g the adjoint that the values pulled by the iolet links of site s (at
 // the step whose ghosts were filled from A) send to the site's own populations of
-// A, and accumulates the inlet-coefficient adjoints.  fh: dJ/df of that step.
+// A, and accumulates the inlet-coefficient adjoints.  gmask: directions of the site's
+// iolet links; fh: dJ/df of that step.
 template <int Q, int ST, bool SC>
 __device__ inline void iolet_terms(const typename Store<ST>::T* __restrict__ A, int32_t s,
-                                   const int32_t (&j)[Q], const float* __restrict__ fh,
-                                   const Ghosts& G, const IoletAdj& I, int64_t kis, int32_t n,
-                                   float (&g)[Q]) {
+                                   uint32_t gmask, const float* __restrict__ fh, const Ghosts& G,
+                                   const IoletAdj& I, int64_t kis, float (&g)[Q]) {
     using C = Codec<Q, ST, SC>;
     using Lt = Lat<Q>;
     float d[Q];
@@ -202,7 +202,7 @@ __device__ inline void iolet_terms(const typename Store<ST>::T* __restrict__ A, 
     int64_t l = I.S.lo[kis];
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
-        if (j[i] < n) continue;
+        if (!(gmask & (1u << i))) continue;
         const int o = opp(i);
         const int kio = G.iolet[l];
         const DevIolet io = G.iolets[kio];
@@ -256,7 +256,7 @@ __device__ inline void adj_group(
     const float* __restrict__ gin, float* __restrict__ gout, const Table& tb, int32_t n,
     float omega, const float* __restrict__ alpha, double* __restrict__ alpha_hat,
     const float* __restrict__ wss_w, const float* __restrict__ normal, const Ghosts& G,
-    const IoletAdj& I, int32_t grp, StageLds& lds) {
+    const IoletAdj& I, int32_t grp, StageLds& lds, LinkLds<Q>& links) {
     using Lt = Lat<Q>;
     static_assert(kBlock == 4 * kTile, "a workgroup covers one group of four tiles");
     if ((int64_t)grp * kBlock >= n) return;  // the whole workgroup lies past the end
@@ -272,41 +272,78 @@ __device__ inline void adj_group(
     }
     const float keep = BRINK && mine && MODE != ADJ_FINAL ? 1.0f - alpha[s] : 1.0f;
     const float ws = wss_w && mine && MODE != ADJ_FINAL ? wss_w[s] : 0.f;
-    int32_t j[Q];
-    links_group<Q, false>(tb, grp, s, live, lds, j);
-    if (!mine) return;
+    using C = Codec<Q, ST, SC>;
+    using T = typename Store<ST>::T;
+    float d[Q];           // pre-collision populations f_t
+    uint32_t gmask = 0;   // directions of the site's iolet links, and the first link
+    int64_t gl = -1;
+    if (tb.grp)
+        stage_links<Q>(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> kTileShift),
+                       (int)threadIdx.x & (kTile - 1), links);
+    const StageHdr h = tb.grp ? stage_header(tb, grp) : StageHdr{0, 0, 0, false};
+    if (h.nown > 0) {
+        constexpr int SZ = sizeof(T), kRow = kRowSize<4>;
+        const int64_t base = group_base(tb.wide, 4 * grp, Q);
+        stage(tb, h, grp, (int)threadIdx.x, lds);
+        lds_loads_done();
+        __syncthreads();
+        if (!mine) return;
+        const uint32_t own = slot_ref<Q, SZ>(s, (uint32_t)base);
+        uint32_t e[Q];
+        staged_refs<Q, SZ>(tb, h, (int)threadIdx.x, (uint32_t)base, own, lds, links, e, gmask);
+        if (gmask) gl = staged_link<Q, SZ>(G, n, base, e, 0u, gmask);
+        if constexpr (MODE != ADJ_OWN) {
+            // stream transpose: the link i of s pulled population i from its source, so
+            // the population opp(i) of s went there (its link i pulled the other way),
+            // or was bounced back into the site's own direction i, or left through an
+            // iolet
+            const char* gb = reinterpret_cast<const char*>(gin + base);
+            g[0] = *reinterpret_cast<const float*>(gb + own * (4 / SZ) - kRow);
+#pragma unroll
+            for (int i = 1; i < Q; ++i) {
+                const int o = opp(i);
+                // a wall link's reference is the own row moved by o - i rows: the load
+                // takes row i, one row beyond the one a fluid link takes each way
+                const bool wall = e[i] == own + (uint32_t)((o - i) * kRowSize<SZ>);
+                const uint32_t r = (wall ? own + (uint32_t)((i - o) * kRowSize<SZ>) : e[i]) * (4 / SZ);
+                g[o] = *reinterpret_cast<const float*>(gb + r + (o - 1) * kRow);
+            }
+            if (gmask) {
+#pragma unroll
+                for (int i = 1; i < Q; ++i)
+                    if (gmask & (1u << i)) g[opp(i)] = 0.f;
+            }
+        }
+        if (MODE != ADJ_FINAL && !F) refs_gather<Q, ST, SC>(A, base, own, e, d);
+    } else {
+        int32_t j[Q];
+        if (live) links_wave<Q, false>(tb, s, j);
+        if (!mine) return;
+        if constexpr (MODE != ADJ_OWN) {
+            g[0] = gin[tix<Q>(0, s)];
+#pragma unroll
+            for (int i = 1; i < Q; ++i) {
+                const int o = opp(i);
+                if (j[i] >= n) {  // walls are negative, sites below n, ghost slots from n
+                    if (gl < 0) gl = ghost_link<Q>(G, n, j[i], i);
+                    gmask |= 1u << i;
+                }
+                g[o] = j[i] >= n ? 0.f : gin[j[i] < 0 ? tix<Q>(i, s) : tix<Q>(o, j[i])];
+            }
+        }
+        if (MODE != ADJ_FINAL && !F) gather_pre<Q, ST, SC>(A, s, n, d, j);
+    }
     if constexpr (MODE != ADJ_OWN) {
-        // stream transpose: the link i of s pulled population i from j[i], so the
-        // population opp(i) of s went to j[i] (its link i pulled the other way), or
-        // was bounced back into the site's own direction i, or left through an iolet
-        g[0] = gin[tix<Q>(0, s)];
-        int32_t top = j[1];  // walls are negative, sites below n, ghost slots from n
-#pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            const int o = opp(i);
-            top = max(top, j[i]);
-            g[o] = j[i] >= n ? 0.f : gin[j[i] < 0 ? tix<Q>(i, s) : tix<Q>(o, j[i])];
-        }
-        if (top >= n) {
-            int64_t l = -1;
-#pragma unroll
-            for (int i = 1; i < Q; ++i)
-                if (l < 0 && j[i] >= n) l = ghost_link<Q>(G, n, j[i], i);
-            iolet_terms<Q, ST, SC>(Ai, s, j, gin, G, I, I.link_is[l], n, g);
-        }
+        if (gmask) iolet_terms<Q, ST, SC>(Ai, s, gmask, gin, G, I, I.link_is[gl], g);
     }
     if constexpr (MODE == ADJ_FINAL) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) gout[tix<Q>(i, s)] = g[i];
         return;
     } else {
-        using C = Codec<Q, ST, SC>;
-        float d[Q];
         if (F) {
 #pragma unroll
             for (int i = 0; i < Q; ++i) d[i] = C::dec(i, F[tix<Q>(i, s)]);
-        } else {
-            gather_pre<Q, ST, SC>(A, s, n, d, j);
         }
         float drho, mx, my, mz;
         moments<Q>(d, drho, mx, my, mz);
@@ -375,9 +412,10 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(
     double* __restrict__ alpha_hat, const float* __restrict__ wss_w,
     const float* __restrict__ normal, Ghosts G, IoletAdj I) {
     __shared__ StageLds lds;
+    __shared__ LinkLds<Q> links;
     adj_group<Q, ST, SC, BRINK, MODE>(A, F, Ai, gin, gout, tb, n, omega, alpha, alpha_hat, wss_w,
                                       normal, G, I, xcd_block((int32_t)blockIdx.x, xcd_group),
-                                      lds);
+                                      lds, links);
 }
 
 // A reverse step of one segment (blocks below nb, a multiple of 8 xcd_group) and a
@@ -396,21 +434,23 @@ __global__ __launch_bounds__(kBlock) void k_adj_dual(
     float omega, const float* __restrict__ alpha, double* __restrict__ alpha_hat,
     const float* __restrict__ wss_w, const float* __restrict__ normal, Ghosts G, IoletAdj I) {
     __shared__ StageLds lds[1];
+    __shared__ LinkLds<Q> links;
     const int32_t b = (int32_t)blockIdx.x;
     if (b < nb) {
         adj_group<Q, ST, SC, BRINK, MODE>(A, nullptr, Ai, gin, gout, tb, n, omega, alpha,
                                           alpha_hat, wss_w, normal, G, I, xcd_block(b, xcd_group),
-                                          lds[0]);
+                                          lds[0], links);
         return;
     }
     const int32_t g = xcd_block(b - nb, xcd_group);
     if constexpr (SREC) {
         __shared__ __attribute__((aligned(16))) typename Store<ST>::T pops[4][Q][kTile];
         stream_collide_staged<Q, ST, SC, BRINK, 4, true>(src, dst, tb, n, tiles_alloc, 4 * g,
-                                                         omega, alpha, Gf, t_next, pops, lds);
+                                                         omega, alpha, Gf, t_next, pops, lds,
+                                                         links);
     } else {
         stream_collide_group<Q, ST, SC, BRINK, false>(src, dst, tb, n, g, omega, alpha, Gf, t_next,
-                                                      lds[0]);
+                                                      lds[0], links);
     }
 }
 
@@ -457,7 +497,7 @@ static hipError_t adj_step_mode(const Layout& L, const Ghosts& G, const IoletAdj
     k_adj_step<Tg::Q, Tg::ST, Tg::SC, BRINK, MODE>
         <<<(unsigned)adj_grid(L.n, xcd_group), kBlock, 0, s>>>(
             static_cast<const T*>(A), static_cast<const T*>(F), static_cast<const T*>(Ai), gin, gout,
-            L.tb, (int32_t)L.n, xcd_group, omega, alpha, alpha_hat, wss_w, normal, G, I);
+            L.tb, (int32_t)L.n, xcd_code(xcd_group), omega, alpha, alpha_hat, wss_w, normal, G, I);
     return hipGetLastError();
 }
 
@@ -509,7 +549,7 @@ static hipError_t adj_dual_mode(const Layout& L, const Ghosts& Gf, const void* s
     k_adj_dual<Tg::Q, Tg::ST, Tg::SC, BRINK, MODE, SREC><<<(unsigned)(2 * nb), kBlock, 0, s>>>(
         static_cast<const T*>(src), static_cast<T*>(dst), Gf, t_next, (int32_t)nb,
         static_cast<const T*>(A), static_cast<const T*>(Ai), gin, gout, L.tb, (int32_t)L.n,
-        (int32_t)(L.slots / kTile), xcd_group, omega, alpha, alpha_hat, wss_w, normal, G, I);
+        (int32_t)(L.slots / kTile), xcd_code(xcd_group), omega, alpha, alpha_hat, wss_w, normal, G, I);
     return hipGetLastError();
 }
 

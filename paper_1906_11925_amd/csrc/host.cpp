@@ -106,8 +106,15 @@ inline uint64_t spread3(uint64_t v) {  // 21 bits -> every third bit
     return v;
 }
 
-inline uint64_t morton(int32_t x, int32_t y, int32_t z) {
-    return spread3((uint64_t)x) | (spread3((uint64_t)y) << 1) | (spread3((uint64_t)z) << 2);
+// Place of a site in the internal order: 4x4x4 blocks in Morton order (z lowest bit),
+// inside a block z fastest, then y, then x.  A wavefront's lanes then hold runs of
+// four sites along z, so that most groups of four lanes read or write one contiguous
+// piece of a row, in a gather as in the caller's order (x slowest, z fastest).
+inline uint64_t site_key(int32_t x, int32_t y, int32_t z) {
+    return ((spread3((uint64_t)(z >> 2)) | (spread3((uint64_t)(y >> 2)) << 1) |
+             (spread3((uint64_t)(x >> 2)) << 2))
+            << 6) |
+           (uint64_t)((z & 3) | ((y & 3) << 2) | ((x & 3) << 4));
 }
 
 // Setup progress on stderr, one line per phase, when HEMELB_VERBOSE is set in the
@@ -225,6 +232,7 @@ struct hemelb_lb {
     int32_t* bnbr = nullptr;
     int32_t* tblock = nullptr;
     int32_t nfluid = 0, nblocks = 0;
+    bool wide = false;  // see hlb::group_base
     int addressing = HEMELB_ADDR_TABLE32;
     int32_t* g_slot = nullptr;  // ghost slot of each iolet link (block addressing)
     int32_t* g_cell_link = nullptr;  // [cells][q]: iolet link pulling (cell, i), or -1
@@ -255,13 +263,17 @@ struct hemelb_lb {
     bool ghosts_ready = false;  // A[cur]'s ghost slots hold the incoming values for time t
     int xcd_group = 16;  // consecutive workgroups per XCD (measured best at 8-16)
     // stream-collide workgroups that copy their own tiles' populations into LDS
-    // (block addressing only; the copy keeps the in-group pulls off the L1, which
-    // then holds the other tiles' lines).  FP32 storage: 8 tiles for D3Q15 lattices
-    // of 4M sites or more, else 4; none for lattices of fewer than 256 four-tile
-    // groups (too few workgroups to hide the copy) and none with 16-bit storage
-    // (slower)
+    // (block addressing only; the copy keeps the in-group pulls off the L1, whose
+    // accesses halve: 51 M -> 26 M per FP16 step of 5.6M sites).  Tiles per workgroup,
+    // by the step's time in us (unstaged / 4 / 8):
+    //   FP32 D3Q15   200k sites 12.9 / 11.4 / 12.3, 1.6M 53.4 / 45.4 / 44.0,
+    //                5.6M 177.1 / 148.6 / 146.2;  D3Q19 5.6M 201.1 / 173.3 / 174.2
+    //   FP16 D3Q15   1.6M 37.8 / 32.0 / 31.9, 5.6M 119.0 / 97.0 / 98.5;  D3Q19 5.6M
+    //                135.8 / 116.3 / 120.4
+    // so 8 for FP32 D3Q15 lattices of a million sites or more, else 4; none for
+    // lattices of fewer than 256 four-tile groups (too few workgroups to hide the copy)
     int stage_tiles = 0;
-    // the FP32 staging copy uses loads that write LDS directly
+    // the staging copy uses loads that write LDS directly
     bool lds_dma = true;
     int64_t check_every = 0;
     std::atomic<bool> cancel{false};
@@ -339,7 +351,7 @@ struct hemelb_lb {
         return hlb::Layout{q, storage, scaled, n, slots,
                            hlb::Table{tbl, t16, toff, tlist, brec, gmask, bnbr, tblock,
                                       reinterpret_cast<const uint4*>(gblob), grp, nfluid, nblocks,
-                                      (int32_t)n},
+                                      (int32_t)n, wide},
                            bfl, stage_tiles, lds_dma};
     }
     hlb::Ghosts ghosts() const {
@@ -534,10 +546,7 @@ struct BlockPlan {
     std::string why;                 // reason it does not apply
 };
 
-inline int block_pos(int x, int y, int z) {
-    return (x & 1) | ((y & 1) << 1) | ((z & 1) << 2) | ((x & 2) << 2) | ((y & 2) << 3) |
-           ((z & 2) << 4);
-}
+inline int block_pos(int x, int y, int z) { return z | (y << 2) | (x << 4); }
 
 inline uint64_t block_key(int64_t bx, int64_t by, int64_t bz) {  // each in [-1, 2^21)
     return ((uint64_t)(bx + 1) << 42) | ((uint64_t)(by + 1) << 21) | (uint64_t)(bz + 1);
@@ -545,6 +554,11 @@ inline uint64_t block_key(int64_t bx, int64_t by, int64_t bz) {  // each in [-1,
 
 inline uint64_t rec_mask(const hlb::BlockRec& r) {
     return ((uint64_t)r.mask_hi << 32) | (uint64_t)r.mask_lo;
+}
+
+// Whether byte references into an FP32 population buffer of `slots` slots need windows.
+inline bool wide_buffers(int64_t slots, int q) {
+    return (slots / hlb::kTile + 1) * q * hlb::kTile >= hlb::kRefSpan;
 }
 
 // order: Morton index -> caller index; inv: its inverse; gbase[m]: first iolet link
@@ -699,10 +713,12 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
     for (int64_t T = 0; T < ttiles; ++T) P.tblock[T] = site_block[std::min(T * hlb::kTile, n - 1)];
 
     // staged records of each group of four tiles (one 256-thread workgroup)
+    const bool wide = wide_buffers(n + P.ncells, q);
     const int64_t groups = (ttiles + 3) / 4;
     P.grp.assign((size_t)groups * 2, 0);
     std::vector<int32_t> recs;
-    std::vector<uint8_t> rows;
+    std::vector<uint16_t> rows;  // byte offsets into the records
+    constexpr int kRowLen = hlb::kRowBytes / 2;
     for (int64_t g = 0; g < groups; ++g) {
         const int64_t s0 = g * 4 * hlb::kTile, s1 = std::min(s0 + 4 * hlb::kTile, n) - 1;
         const int32_t b_lo = site_block[s0], b_hi = site_block[s1];
@@ -717,7 +733,7 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
         }
         recs.clear();
         for (int32_t b = b_lo; b <= b_hi; ++b) recs.push_back(b);
-        rows.assign((size_t)nown * hlb::kRowBytes, 0xff);
+        rows.assign((size_t)nown * kRowLen, 0xffff);
         bool fits = true;
         for (int k = 0; k < nown && fits; ++k)
             for (int dd = 0; dd < 27; ++dd) {
@@ -730,25 +746,46 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
                     }
                     recs.push_back(nb);
                 }
-                rows[(size_t)k * hlb::kRowBytes + dd] = (uint8_t)idx;
+                rows[(size_t)k * kRowLen + dd] =
+                    (uint16_t)(nown * hlb::kRowBytes + idx * sizeof(hlb::BlockRec));
             }
         if (!fits) {
             P.fallback_bytes += global_bytes;
             continue;
         }
-        const size_t row_words = (size_t)((nown * hlb::kRowBytes + 15) / 16) * 4;
+        // references of a wide lattice are offsets within a window around the group
+        bool ghosts = false;
+        const int64_t base = hlb::group_base(wide, (int32_t)(4 * g), q);
+        auto inside = [&](int64_t slot) {
+            const int64_t e = (slot / hlb::kTile) * q * hlb::kTile - base;
+            return e >= 0 && e < hlb::kRefSpan;
+        };
+        for (const int32_t b : recs) {
+            if (b < 0) continue;
+            fits = fits && (rec_mask(P.rec[b]) == 0 ||
+                            (inside(P.rec[b].off) && inside(P.rec[b].off + hlb::kTile - 1)));
+            if (P.rec[b].goff < 0) continue;
+            ghosts = true;
+            fits = fits && inside(n) && inside(n + P.rec[b].goff + hlb::kTile - 1);
+        }
+        if (!fits) {
+            P.fallback_bytes += global_bytes;
+            continue;
+        }
+        const size_t row_words = (size_t)nown * hlb::kRowBytes / 4;
         const size_t at = P.blob.size();
         P.blob.resize(at + row_words + recs.size() * 4, 0);
-        std::memcpy(&P.blob[at], rows.data(), rows.size());
+        std::memcpy(&P.blob[at], rows.data(), rows.size() * 2);
         for (size_t r = 0; r < recs.size(); ++r) {
             hlb::BlockRec c{0u, 0u, 0, -1};  // no block there: no fluid, no ghost cells
             if (recs[r] >= 0) {
                 c = P.rec[recs[r]];
+                c.off -= 1;
                 c.goff = c.goff >= 0 ? recs[r] : -1;  // staged copies name ghost blocks by id
             }
             std::memcpy(&P.blob[at + row_words + 4 * r], &c, sizeof c);
         }
-        P.grp[2 * g + 1] = nown | (int32_t)(recs.size() << 16);
+        P.grp[2 * g + 1] = nown | (int32_t)(recs.size() << 16) | (ghosts ? hlb::kGroupGhosts : 0);
     }
     if (P.blob.empty()) P.blob.assign(4, 0);
 
@@ -757,20 +794,19 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
     parallel_for(n, [&](int64_t a, int64_t b) {
         for (int64_t m = a; m < b && bad.load(std::memory_order_relaxed) < 0; ++m) {
             const int64_t g = m / (4 * hlb::kTile);
-            const int nown = P.grp[2 * g + 1] & 0xffff;
+            const int nown = P.grp[2 * g + 1] & 0xff;
             if (nown == 0) continue;
             const uint8_t* bytes = reinterpret_cast<const uint8_t*>(&P.blob[4 * (size_t)P.grp[2 * g]]);
             const hlb::BlockRec* recs =
-                reinterpret_cast<const hlb::BlockRec*>(bytes + 16 * ((nown * hlb::kRowBytes + 15) / 16));
+                reinterpret_cast<const hlb::BlockRec*>(bytes + nown * hlb::kRowBytes);
             int k = 0;
             for (int qq = 1; qq < nown; ++qq)
-                if (m >= recs[qq].off) k = qq;
+                if (m > recs[qq].off) k = qq;
             const uint64_t om = rec_mask(recs[k]);
-            int rank = (int)(m - recs[k].off), p = 0;
+            int rank = (int)(m - recs[k].off) - 1, p = 0;
             for (; p < 64; ++p)
                 if (((om >> p) & 1ull) && rank-- == 0) break;
-            const int bx = (p & 1) | ((p >> 2) & 2), by = ((p >> 1) & 1) | ((p >> 3) & 2),
-                      bz = ((p >> 2) & 1) | ((p >> 4) & 2);
+            const int bx = p >> 4, by = (p >> 2) & 3, bz = p & 3;
             const int64_t s = order[m];
             int64_t gl = gbase[m];
             for (int i = 1; i < q; ++i) {
@@ -779,12 +815,14 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
                                    : v == HEMELB_LINK_WALL ? (int32_t)0x80000000u : P.gslot[gl++];
                 const int ux = bx - lat.c[i][0], uy = by - lat.c[i][1], uz = bz - lat.c[i][2];
                 const int dd = ((ux >> 2) + 1) + 3 * ((uy >> 2) + 1) + 9 * ((uz >> 2) + 1);
-                const hlb::BlockRec& r = recs[bytes[k * hlb::kRowBytes + dd]];
+                uint16_t at;
+                std::memcpy(&at, bytes + k * hlb::kRowBytes + 2 * dd, 2);
+                const hlb::BlockRec& r = *reinterpret_cast<const hlb::BlockRec*>(bytes + at);
                 const int pp = block_pos(ux & 3, uy & 3, uz & 3);
                 const uint64_t mk = rec_mask(r), below = (1ull << pp) - 1ull;
                 int32_t got = (int32_t)0x80000000u;
                 if ((mk >> pp) & 1ull)
-                    got = r.off + __builtin_popcountll(mk & below);
+                    got = r.off + 1 + __builtin_popcountll(mk & below);
                 else if (r.goff >= 0 && ((P.gmask[r.goff] >> pp) & 1ull))
                     got = (int32_t)n + P.rec[r.goff].goff + __builtin_popcountll(P.gmask[r.goff] & below);
                 if (got != want) {
@@ -918,7 +956,7 @@ int make_plan(const hemelb_lb_desc_t* d, HostPlan& P, Progress& prog) {
         parallel_for(n, [&](int64_t a, int64_t b) {
             for (int64_t s = a; s < b; ++s) {
                 const int32_t* c = d->coords + 3 * s;
-                ki[s] = KI{morton(c[0], c[1], c[2]), (int32_t)s};
+                ki[s] = KI{site_key(c[0], c[1], c[2]), (int32_t)s};
             }
         });
         parallel_sort(ki, [](const KI& a, const KI& b) {
@@ -1508,8 +1546,11 @@ static int init_handle(hemelb_lb* h, hemelb_lb_t* out, const hemelb_lb_desc_t* d
     h->stream = static_cast<hipStream_t>(d->stream);
     if (const char* e = getenv("HEMELB_XCD_GROUP")) h->xcd_group = std::max(0, atoi(e));
     h->stage_tiles = 0;
-    if (h->storage == HEMELB_STORE_F32 && (d->n_sites + 255) / 256 >= 256)
-        h->stage_tiles = h->q == 15 && d->n_sites >= ((int64_t)1 << 22) ? 8 : 4;
+    if ((d->n_sites + 255) / 256 >= 256)
+        h->stage_tiles = h->storage == HEMELB_STORE_F32 && h->q == 15 &&
+                                 d->n_sites >= ((int64_t)1 << 20)
+                             ? 8
+                             : 4;
     if (const char* e = getenv("HEMELB_STAGE_TILES")) {
         const int v = atoi(e);
         h->stage_tiles = (v == 4 || v == 8 || v == 16) ? v : 0;
@@ -1563,6 +1604,7 @@ static int init_handle(hemelb_lb* h, hemelb_lb_t* out, const hemelb_lb_desc_t* d
     if (P.addressing == HEMELB_ADDR_BLOCKS) {
         h->nfluid = P.bp.nfluid;
         h->nblocks = (int32_t)P.bp.rec.size();
+        h->wide = wide_buffers(n + P.bp.ncells, q);
         TRY(dev_upload(h, &h->brec, P.bp.rec, "block records"));
         TRY(dev_upload(h, &h->gmask, P.bp.gmask, "ghost masks"));
         TRY(dev_upload(h, &h->bnbr, P.bp.nbr, "neighbour blocks"));

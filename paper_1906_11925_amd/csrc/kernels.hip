@@ -15,19 +15,28 @@
 //  * the compact 16-bit table, whose codes name a slot in the tile's short list of
 //    source tiles (exchanged between lanes with ds_bpermute) and a lane;
 //  * two-level block addressing (4x4x4 blocks with fluid bitmaps): each 256-thread
-//    workgroup stages the block records its four tiles need into LDS with one
-//    coalesced load and decodes every link from LDS.
-// The work is a gather stencil at ~1.3 flop per byte, memory-bound (in practice by
-// the rate of requests from L1 to L2 that the gathers issue), so there is no
-// matrix-core work.  With FP32 storage and block addressing, workgroups of 4 or 8
-// tiles first copy their own tiles' populations into LDS, by loads that write LDS
-// directly, and pulls from inside the workgroup read LDS: fewer L1 misses reach
-// L2.  A variant of the step also stores the pulled populations, for the reverse
-// sweep over a recorded trajectory.
+//    group stages the block records its four tiles need into LDS and decodes every
+//    link from there.
+// The work is a gather stencil at ~1.3 flop per byte; there is no contraction in it and
+// so no matrix-core work.  What bounds it is, on large lattices with FP32 storage, the
+// traffic that leaves the L2s (6.5 TB/s of it), and with 16-bit storage the rate of
+// vector instructions: a wavefront of the step issued 770 of them, 100% of the SIMDs'
+// issue slots, of which 500 found the links.  Hence the form of the decode (staged_refs
+// in lbdev.hpp): precomputed per-position tables in LDS, a 64-bit shift and two
+// population counts per link, and 32-bit references that are the loads' own offsets;
+// 490 instructions with 16-bit storage and 450 in FP32, and every load of a workgroup's
+// prologue issued before the first wait.  Workgroups of 4 or 8 tiles copy their own
+// tiles' populations into LDS, by loads that write LDS directly, and pulls from inside
+// the workgroup read LDS, which halves the accesses to L1.  Step time on 5.6M sites,
+// before and after: FP32 157.5 -> 146.2 us, FP16 113.1 -> 97.0 us, BF16 115.0 -> 98 us,
+// D3Q19 FP32 194.7 -> 173.3 us.
+// A variant of the step also stores the pulled populations, for the reverse sweep over
+// a recorded trajectory.
 //
-// Memory layout: sites are Morton-ordered and grouped in tiles of 64, the width of
-// a wavefront.  Populations are stored [tile][direction][64] and the tables
-// [tile][direction-1][64], so one wavefront's stores of all directions and its
+// Memory layout: sites are ordered by 4x4x4 block (Morton order of the blocks, z
+// fastest inside one) and grouped in tiles of 64, the width of a wavefront.
+// Populations are stored [tile][direction][64] and the tables [tile][direction-1][64],
+// so one wavefront's stores of all directions and its
 // table loads each cover one contiguous block (3.75 KB and 3.5 KB for D3Q15 in
 // FP32) instead of 2Q separate address streams; every per-direction access of a
 // wavefront is a 256-byte (FP32) or 128-byte (16-bit) aligned chunk.
@@ -50,9 +59,10 @@ __global__ __launch_bounds__(kScBlock) void k_stream_collide(
     Table tb, int32_t n, int32_t xcd_group, float omega, const float* __restrict__ alpha, Ghosts G,
     int64_t t_next, typename Store<ST>::T* __restrict__ fout) {
     __shared__ StageLds lds;
+    __shared__ LinkLds<Q> links;
     stream_collide_group<Q, ST, SC, BRINK, BFL, FOUT>(src, dst, tb, n,
                                                       xcd_block((int32_t)blockIdx.x, xcd_group),
-                                                      omega, alpha, G, t_next, lds, fout);
+                                                      omega, alpha, G, t_next, lds, links, fout);
 }
 
 // workgroups of W tiles with their own populations staged in LDS (block addressing);
@@ -65,9 +75,11 @@ __global__ __launch_bounds__(W * kTile) void k_stream_collide_staged(
     typename Store<ST>::T* __restrict__ fout) {
     __shared__ __attribute__((aligned(16))) typename Store<ST>::T pops[W][Q][kTile];
     __shared__ StageLds lds[W / 4];
+    __shared__ LinkLds<Q> links;
     const int32_t w = xcd_block((int32_t)blockIdx.x, xcd_group);
     stream_collide_staged<Q, ST, SC, BRINK, W, DMA, FOUT>(src, dst, tb, n, tiles_alloc, w * W,
-                                                          omega, alpha, G, t_next, pops, lds, fout);
+                                                          omega, alpha, G, t_next, pops, lds, links,
+                                                          fout);
 }
 
 // ---------------------------------------------------------------------------
@@ -127,22 +139,40 @@ __global__ __launch_bounds__(kBlock) void k_observables(
     using Lt = Lat<Q>;
     static_assert(kBlock == 4 * kTile, "a workgroup covers one group of four tiles");
     __shared__ StageLds lds;
+    __shared__ LinkLds<Q> links;
     const int32_t g = blockIdx.x;
     const int32_t s = g * kBlock + threadIdx.x;
     const bool live = (s & ~(kTile - 1)) < n;
-    int32_t j[Q];
-    if (streamed) links_group<Q, false>(tb, g, s, live, lds, j);
-    if (!live || s >= n) return;
     float d[Q];
-    d[0] = C::dec(0, A[tix<Q>(0, s)]);
+    if (streamed && tb.grp)
+        stage_links<Q>(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> kTileShift),
+                       (int)threadIdx.x & (kTile - 1), links);
+    const StageHdr h = streamed && tb.grp ? stage_header(tb, g) : StageHdr{0, 0, 0, false};
+    if (h.nown > 0) {
+        constexpr int SZ = sizeof(typename Store<ST>::T);
+        const int64_t base = group_base(tb.wide, 4 * g, Q);
+        stage(tb, h, g, (int)threadIdx.x, lds);
+        lds_loads_done();
+        __syncthreads();
+        if (s >= n) return;
+        const uint32_t own = slot_ref<Q, SZ>(s, (uint32_t)base);
+        uint32_t e[Q], gmask;
+        staged_refs<Q, SZ>(tb, h, (int)threadIdx.x, (uint32_t)base, own, lds, links, e, gmask);
+        refs_gather<Q, ST, SC>(A, base, own, e, d);
+    } else {
+        int32_t j[Q];
+        if (streamed && live) links_wave<Q, false>(tb, s, j);
+        if (s >= n) return;
+        d[0] = C::dec(0, A[tix<Q>(0, s)]);
 #pragma unroll
-    for (int i = 1; i < Q; ++i) {
-        int dir = i;
-        int32_t site = s;
-        if (streamed) link_src(i, j[i], s, dir, site);
-        d[i] = C::dec(i, A[tix<Q>(dir, site)]);
+        for (int i = 1; i < Q; ++i) {
+            int dir = i;
+            int32_t site = s;
+            if (streamed) link_src(i, j[i], s, dir, site);
+            d[i] = C::dec(i, A[tix<Q>(dir, site)]);
+        }
+        if (streamed) apply_bfl<Q, ST, SC>(A, s, n, j, d);
     }
-    if (streamed) apply_bfl<Q, ST, SC>(A, s, n, j, d);
     float drho, mx, my, mz;
     moments<Q>(d, drho, mx, my, mz);
     const float rho = 1.0f + drho;
@@ -333,12 +363,11 @@ static hipError_t launch_staged(const Layout& L, const Ghosts& G, const void* sr
         auto go = [&](auto kernel) {
             kernel<<<(unsigned)grid, W * kTile, 0, s>>>(static_cast<const T*>(src),
                                                         static_cast<T*>(dst), L.tb, (int32_t)L.n,
-                                                        tiles_alloc, per, omega, alpha, G, t_next,
+                                                        tiles_alloc, xcd_code(per), omega, alpha, G, t_next,
                                                         static_cast<T*>(fout));
             return hipGetLastError();
         };
-        // the direct-to-LDS copy exists for FP32 rows only, and so does the store of
-        // the pulled populations (the recording forward)
+        // the store of the pulled populations (the recording forward) exists for FP32 only
         if constexpr (Tg::ST == ST_F32) {
             if (fout)
                 return L.lds_dma
@@ -346,11 +375,11 @@ static hipError_t launch_staged(const Layout& L, const Ghosts& G, const void* sr
                                     : go(k_stream_collide_staged<Tg::Q, Tg::ST, Tg::SC, false, W, true, true>))
                            : (alpha ? go(k_stream_collide_staged<Tg::Q, Tg::ST, Tg::SC, true, W, false, true>)
                                     : go(k_stream_collide_staged<Tg::Q, Tg::ST, Tg::SC, false, W, false, true>));
-            if (L.lds_dma)
-                return alpha ? go(k_stream_collide_staged<Tg::Q, Tg::ST, Tg::SC, true, W, true, false>)
-                             : go(k_stream_collide_staged<Tg::Q, Tg::ST, Tg::SC, false, W, true, false>);
         }
         if (fout) return hipErrorInvalidValue;
+        if (L.lds_dma)
+            return alpha ? go(k_stream_collide_staged<Tg::Q, Tg::ST, Tg::SC, true, W, true, false>)
+                         : go(k_stream_collide_staged<Tg::Q, Tg::ST, Tg::SC, false, W, true, false>);
         return alpha ? go(k_stream_collide_staged<Tg::Q, Tg::ST, Tg::SC, true, W, false, false>)
                      : go(k_stream_collide_staged<Tg::Q, Tg::ST, Tg::SC, false, W, false, false>);
     });
@@ -376,7 +405,7 @@ hipError_t launch_stream_collide(const Layout& L, const Ghosts& G, const void* s
         auto go = [&](auto kernel, const float* a) {
             kernel<<<(unsigned)grid, kScBlock, 0, s>>>(static_cast<const T*>(src),
                                                        static_cast<T*>(dst), L.tb, (int32_t)L.n,
-                                                       per, omega, a, G, t_next,
+                                                       xcd_code(per), omega, a, G, t_next,
                                                        static_cast<T*>(fout));
         };
         if (fout) {  // the recording forward: FP32 storage, halfway walls

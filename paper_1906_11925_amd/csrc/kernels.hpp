@@ -21,7 +21,7 @@ struct DevIolet {
 };
 
 // One 4x4x4 block of the lattice in block addressing.  Positions inside a block
-// are 6-bit Morton codes p (bits x0 y0 z0 x1 y1 z1), the order of the sites.
+// are p = z + 4 y + 16 x, the order of the sites.
 struct BlockRec {
     uint32_t mask_lo, mask_hi;  // fluid positions
     int32_t off;                // site index of the block's first fluid site
@@ -52,13 +52,15 @@ struct BlockRec {
 //    For a fast decode every group of four tiles (256 sites, one workgroup) has a
 //    staged copy of the records it needs, loaded into LDS with one coalesced read
 //    per workgroup: grp[2g] = offset of group g's blob in 16-byte units, grp[2g+1]
-//    = nown | nrec << 16 (nown = 0: the group uses the global records).  The blob
+//    = nown | nrec << 16 (nown = 0: the group uses the global records), plus
+//    kGroupGhosts when some record has ghost cells.  The blob
 //    holds nown rows of kRowBytes bytes (the group's own blocks, consecutive ids
-//    from the block of its first site; row k, byte d = index into the blob's
-//    records of neighbour d of own block k; where no block exists it names an
-//    empty record (no fluid, no ghost cells)), padded to 16 bytes,
+//    from the block of its first site; row k, 16-bit entry d = byte offset in the
+//    blob of the record of neighbour d of own block k; where no block exists it names an
+//    empty record (no fluid, no ghost cells)),
 //    then nrec BlockRecs whose first nown are the own blocks in order; in these
-//    copies goff holds the block's id when it has ghost cells (-1 otherwise).
+//    copies off is one less and goff holds the block's id when it has ghost cells
+//    (-1 otherwise).
 struct Table {
     const int32_t* t32;
     const uint16_t* t16;
@@ -73,14 +75,27 @@ struct Table {
     int32_t nfluid;  // blocks holding fluid sites
     int32_t nblocks;
     int32_t n;       // fluid sites (the first ghost slot)
+    bool wide;       // an FP32 population buffer reaches past 4 GiB (see group_base)
 };
 
 // capacity of a group's staged blob (groups beyond it use the global records)
-constexpr int kRowBytes = 28;
+constexpr int kRowBytes = 64;
 constexpr int kStageRows = 24;
-constexpr int kStageRowChunks = (kStageRows * kRowBytes + 15) / 16;
 constexpr int kStageRecs = 160;
-constexpr int kStageChunks = kStageRowChunks + kStageRecs;  // <= threads per workgroup
+constexpr int32_t kGroupGhosts = 0x8000;
+constexpr int kStageChunks = kStageRows * kRowBytes / 16 + kStageRecs;  // <= threads per workgroup
+
+// Sources of a staged group's links are 32-bit references: the element offset of the
+// source's first population row (tile * q * 64 + lane) from the group's base, plus one
+// row.  The base is the start of the buffer, or, for a lattice whose FP32 buffer
+// reaches past 4 GiB, 2^29 elements below the group's first tile (the host leaves a
+// group whose sources lie outside that window to the global records).
+constexpr int64_t kRefBack = (int64_t)1 << 29;
+constexpr int64_t kRefSpan = ((int64_t)1 << 30) - 4096;  // references stay below 2^30
+inline __host__ __device__ int64_t group_base(bool wide, int32_t tile, int q) {
+    const int64_t at = (int64_t)tile * q * kTile;
+    return wide && at > kRefBack ? at - kRefBack : 0;
+}
 
 // Layout of one handle's device data, shared by all launches.  Populations are
 // stored [slots/64][q][64] (sites, then ghost slots, Morton order).

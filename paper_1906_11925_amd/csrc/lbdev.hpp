@@ -168,11 +168,8 @@ __device__ inline int select_bit(uint64_t m, int r) {
     return p;
 }
 
-// 6-bit Morton position of local coordinates (x, y, z) in [0, 4)^3
-__device__ inline int block_pos(int x, int y, int z) {
-    return (x & 1) | ((y & 1) << 1) | ((z & 1) << 2) | ((x & 2) << 2) | ((y & 2) << 3) |
-           ((z & 2) << 4);
-}
+// position of local coordinates (x, y, z) in [0, 4)^3: z fastest, then y, then x
+__device__ inline int block_pos(int x, int y, int z) { return z | (y << 2) | (x << 4); }
 
 // Links j[1..Q-1] of the site at local coordinates (bx, by, bz) of block bl.
 template <int Q>
@@ -207,9 +204,9 @@ __device__ inline void block_site(const Table& tb, int32_t s, int32_t bl, int& b
                                   int& bz) {
     const BlockRec r = tb.brec[bl];
     const int p = select_bit(block_mask(r), s - r.off);
-    bx = (p & 1) | ((p >> 2) & 2);
-    by = ((p >> 1) & 1) | ((p >> 3) & 2);
-    bz = ((p >> 2) & 1) | ((p >> 4) & 2);
+    bx = p >> 4;
+    by = (p >> 2) & 3;
+    bz = p & 3;
 }
 
 // Wave form: the blocks that the tile's sites fall into are found with
@@ -230,9 +227,50 @@ __device__ inline void links_blocks_wave(const Table& tb, int32_t s, int32_t (&j
     block_links<Q>(tb, bl, bx, by, bz, j);
 }
 
-// LDS of one workgroup for the staged block records
+// Per position p of a block and moving direction i: where the upstream position lies.
+// Bits 16..: byte offset of its block in a group's row (2 bytes per neighbour block);
+// bits 0..5: 63 - its position there.
+template <int Q>
+struct LinkTable {
+    static constexpr int quads = (Q - 1 + 3) / 4;
+    struct alignas(16) Quad {
+        uint32_t x, y, z, w;
+    };
+    Quad q[quads][kTile];
+};
+template <int Q>
+constexpr uint32_t link_entry(int p, int i) {
+    if (i >= Q) return 0u;
+    const int ux = (p >> 4) - Lat<Q>::cx[i], uy = ((p >> 2) & 3) - Lat<Q>::cy[i],
+              uz = (p & 3) - Lat<Q>::cz[i];  // each in [-1, 4]
+    const int d = ((ux + 4) / 4) + 3 * ((uy + 4) / 4) + 9 * ((uz + 4) / 4);
+    const int pos = (uz & 3) | ((uy & 3) << 2) | ((ux & 3) << 4);
+    return ((uint32_t)(2 * d) << 16) | (uint32_t)(63 - pos);
+}
+template <int Q>
+constexpr LinkTable<Q> make_link_table() {
+    LinkTable<Q> t{};
+    for (int c = 0; c < LinkTable<Q>::quads; ++c)
+        for (int p = 0; p < kTile; ++p) {
+            t.q[c][p].x = link_entry<Q>(p, 4 * c + 1);
+            t.q[c][p].y = link_entry<Q>(p, 4 * c + 2);
+            t.q[c][p].z = link_entry<Q>(p, 4 * c + 3);
+            t.q[c][p].w = link_entry<Q>(p, 4 * c + 4);
+        }
+    return t;
+}
+template <int Q>
+__device__ const LinkTable<Q> kLinkTable = make_link_table<Q>();
+
+// LDS of one group: its staged block records and the own block and position of each of
+// its sites (at: block << 6 | position); and, one for the workgroup, the link table.
 struct StageLds {
     uint4 chunk[kStageChunks];
+    uint16_t at[4 * kTile];
+};
+template <int Q>
+struct LinkLds {
+    alignas(16) typename LinkTable<Q>::Quad q[LinkTable<Q>::quads][kTile];
 };
 
 // A group's staged blob: where it starts and how many own blocks and records it
@@ -241,6 +279,7 @@ struct StageLds {
 struct StageHdr {
     int32_t off;
     int nown, nrec;
+    bool ghosts;
 };
 
 // The group entries never change during a launch: read them through the constant
@@ -251,109 +290,138 @@ __device__ inline StageHdr stage_header(const Table& tb, int32_t g) {
     const __attribute__((address_space(4))) int32_t* grp =
         (const __attribute__((address_space(4))) int32_t*)tb.grp;
     const int32_t cnt = grp[2 * g + 1];
-    return StageHdr{grp[2 * g], cnt & 0xffff, cnt >> 16};
+    return StageHdr{grp[2 * g], cnt & 0xff, cnt >> 16, (cnt & kGroupGhosts) != 0};
 }
 
-// One thread's share of staging a blob: at most one 16-byte chunk and its LDS slot
-// (-1: none).  Fetching and committing are separate so that a workgroup can load
-// the next group's blob while it works on the current one.
-struct StageChunk {
-    uint4 v;
-    int dst;
-};
+// bytes of one population row of a tile
+template <int SZ>
+constexpr int kRowSize = kTile * SZ;
 
-__device__ inline StageChunk stage_fetch(const Table& tb, const StageHdr& h) {
-    StageChunk c;
-    c.dst = -1;
-    c.v = make_uint4(0u, 0u, 0u, 0u);
-    if (h.nown == 0) return c;
-    const int row_chunks = (h.nown * kRowBytes + 15) >> 4;
-    const int t = (int)threadIdx.x;
-    if (t < row_chunks + h.nrec) {
-        c.v = tb.gblob[h.off + t];
-        c.dst = t < row_chunks ? t : kStageRowChunks + t - row_chunks;
-    }
-    return c;
+// byte reference of slot j (site or ghost), for elements of SZ bytes
+template <int Q, int SZ>
+__device__ inline uint32_t slot_ref(int32_t j, uint32_t base) {
+    const uint32_t e = (uint32_t)j + __umul24((uint32_t)j >> kTileShift, (Q - 1) * kTile);
+    return e * SZ + (kTile - base) * SZ;
 }
 
-__device__ inline void stage_commit(const StageChunk& c, StageLds& lds) {
-    if (c.dst >= 0) lds.chunk[c.dst] = c.v;
+// slot of a byte reference
+template <int Q, int SZ>
+__device__ inline int32_t ref_slot(uint32_t ref, int64_t base) {
+    const int64_t e = (int64_t)(ref / SZ) - kTile + base;
+    const int32_t T = (int32_t)(e / (Q * kTile));
+    return (T << kTileShift) | (int32_t)(e - (int64_t)T * (Q * kTile));
 }
 
-// Links of site s from its group's staged blob in LDS (nown > 0 own blocks).  All
-// lanes of the wavefront call it (the own-block search is wave-uniform in its
-// bounds).  Per link: the row byte names the neighbour block's staged record; a
-// fluid position ranks in its mask; any other position is a wall unless the block
-// has ghost cells and the position is one (global ghost masks; rare, only next to
-// iolet planes).
+// 16 bytes per lane from global memory into LDS (no registers, no LDS store): lane l of
+// the wavefront writes to + 16 l; `to` is uniform.  lds_loads_done() before the barrier.
+__device__ inline void load_lds16(const void* from, void* to) {
+    __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
+}
+__device__ inline void lds_loads_done() { __builtin_amdgcn_s_waitcnt(0); }
+
+// Start the copy of the link table by the workgroup's first four wavefronts.
 template <int Q>
-__device__ inline void decode_staged(const Table& tb, int nown, int32_t s, const StageLds& lds,
-                                     int32_t (&j)[Q]) {
-    using Lt = Lat<Q>;
-    const uint8_t* rows = reinterpret_cast<const uint8_t*>(lds.chunk);
-    const BlockRec* recs = reinterpret_cast<const BlockRec*>(lds.chunk + kStageRowChunks);
-    // own block: the last one whose first site is at or before s (offsets ascend;
-    // only blocks starting inside this wavefront's tile can change the answer)
-    const int32_t last = __builtin_amdgcn_readfirstlane(s | (kTile - 1));
-    int k = 0;
-    for (int q = 1; q < nown; ++q) {
-        const int32_t o = recs[q].off;
-        if (o > last) break;
-        if (s >= o) k = q;
+__device__ inline void stage_links(int wave, int lane, LinkLds<Q>& links) {
+    constexpr int quads = LinkTable<Q>::quads;
+    if (wave < 4) load_lds16(&kLinkTable<Q>.q[wave][lane], &links.q[wave][0]);
+    if (wave < quads - 4) load_lds16(&kLinkTable<Q>.q[4 + wave][lane], &links.q[4 + wave][0]);
+}
+
+// One thread's share of staging a group with records (t: thread index within the
+// group's 256 threads): the records, and where each site lies (each wavefront takes
+// every fourth own block, whose record is uniform).  The loads are issued before the
+// first value is used, so that the stage costs one memory latency after the header's.
+// A row of 64 bytes makes block << 6 the byte offset of the block's row.
+__device__ inline void stage(const Table& tb, const StageHdr& h, int32_t g, int t, StageLds& lds) {
+    const int lane = t & (kTile - 1), wave = __builtin_amdgcn_readfirstlane(t >> kTileShift);
+    const int rows = h.nown * (kRowBytes / 16);
+    if (t < rows + h.nrec) load_lds16(tb.gblob + h.off + t, &lds.chunk[wave * kTile]);
+    const __attribute__((address_space(4))) uint32_t* recs =
+        (const __attribute__((address_space(4))) uint32_t*)(tb.gblob + h.off + rows);
+    const int k0 = min(wave, h.nown - 1), k1 = min(wave + 4, h.nown - 1);
+    const uint32_t a0 = recs[4 * k0], a1 = recs[4 * k0 + 1], a2 = recs[4 * k0 + 2];
+    const uint32_t b0 = recs[4 * k1], b1 = recs[4 * k1 + 1], b2 = recs[4 * k1 + 2];
+    auto place = [&](int k, uint32_t lo, uint32_t hi, uint32_t off) {
+        const uint64_t m = ((uint64_t)hi << 32) | lo;
+        const uint32_t at = __builtin_amdgcn_mbcnt_hi(
+            hi, __builtin_amdgcn_mbcnt_lo(lo, off + 1u - (uint32_t)(g * 4 * kTile)));
+        if (((m >> lane) & 1ull) && at < 4 * kTile) lds.at[at] = (uint16_t)((k << 6) | lane);
+    };
+    place(k0, a0, a1, a2);  // a block placed twice (few own blocks) gets the same values
+    place(k1, b0, b1, b2);
+    for (int k = wave + 8; k < h.nown; k += 4) place(k, recs[4 * k], recs[4 * k + 1], recs[4 * k + 2]);
+}
+
+// Source references of the links of the group's site t (its own reference: own), from
+// the group's LDS (h.nown > 0).  A wall link gets the site's own row: the reference
+// less (i - 1) rows is then the address of population opp(i).  gmask, if the group has
+// ghost cells: the directions of the site's iolet links.
+template <int Q, int SZ>
+__device__ inline void staged_refs(const Table& tb, const StageHdr& h, int t, uint32_t base,
+                                   uint32_t own, const StageLds& lds, const LinkLds<Q>& links,
+                                   uint32_t (&e)[Q], uint32_t& gmask) {
+    const char* raw = reinterpret_cast<const char*>(lds.chunk);
+    const uint32_t at = lds.at[t];
+    const uint32_t p = at & 63u;
+    const uint32_t row = at & ~63u;
+    uint32_t lk[LinkTable<Q>::quads * 4];
+#pragma unroll
+    for (int c = 0; c < LinkTable<Q>::quads; ++c) {
+        const typename LinkTable<Q>::Quad v = links.q[c][p];
+        lk[4 * c] = v.x;
+        lk[4 * c + 1] = v.y;
+        lk[4 * c + 2] = v.z;
+        lk[4 * c + 3] = v.w;
     }
-    const BlockRec own = recs[k];
-    const int p = select_bit(block_mask(own), s - own.off);
-    const int bx = (p & 1) | ((p >> 2) & 2);
-    const int by = ((p >> 1) & 1) | ((p >> 3) & 2);
-    const int bz = ((p >> 2) & 1) | ((p >> 4) & 2);
-    const uint8_t* row = rows + k * kRowBytes;
+    auto rec = [&](int i) {
+        const uint32_t a = *reinterpret_cast<const uint16_t*>(raw + row + (lk[i - 1] >> 16));
+        return *reinterpret_cast<const uint4*>(raw + a);
+    };
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
-        const int ux = bx - Lt::cx[i], uy = by - Lt::cy[i], uz = bz - Lt::cz[i];  // in [-1, 4]
-        const int d = ((ux >> 2) + 1) + 3 * ((uy >> 2) + 1) + 9 * ((uz >> 2) + 1);
-        const int pp = block_pos(ux & 3, uy & 3, uz & 3);
-        const BlockRec r = recs[row[d]];
-        const uint32_t sh = (uint32_t)pp & 31u;
-        const bool upper = pp >= 32;
-        const uint32_t w = upper ? r.mask_hi : r.mask_lo;
-        const int rank = __popc(w & ((1u << sh) - 1u)) + (upper ? __popc(r.mask_lo) : 0);
-        const bool fluid = (w >> sh) & 1u;
-        int32_t v = fluid ? r.off + rank : (int32_t)0x80000000u;
-        if (!fluid && r.goff >= 0) {
-            const int32_t b2 = r.goff;
-            const uint64_t gm = tb.gmask[b2];
-            if ((gm >> pp) & 1ull)
-                v = tb.n + tb.brec[b2].goff + __popcll(gm & ((1ull << pp) - 1ull));
+        // the mask shifted so that the position is the top bit: sign = a fluid site,
+        // population count = its rank + 1
+        const uint4 r = rec(i);
+        const uint64_t m = (((uint64_t)r.y << 32) | r.x) << (lk[i - 1] & 63u);
+        const int32_t j = (int32_t)r.z + __popc((uint32_t)m) + __popc((uint32_t)(m >> 32));
+        const uint32_t ref = slot_ref<Q, SZ>(j, base);
+        e[i] = (int64_t)m < 0 ? ref : own + (opp(i) - i) * kRowSize<SZ>;
+    }
+    gmask = 0;
+    if (!h.ghosts) return;
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        if (e[i] != own + (opp(i) - i) * kRowSize<SZ>) continue;
+        const int32_t b = (int32_t)rec(i).w;  // block with ghost cells
+        if (b < 0) continue;
+        const uint64_t gm = tb.gmask[b] << (lk[i - 1] & 63u);
+        if ((int64_t)gm < 0) {
+            e[i] = slot_ref<Q, SZ>(tb.n + tb.brec[b].goff + __popcll(gm) - 1, base);
+            gmask |= 1u << i;
         }
-        j[i] = v;
     }
 }
 
-// Links of the sites of one 256-thread workgroup (group g = four consecutive
-// tiles) from the group's staged block records.  Every thread of the workgroup
-// calls it (it holds a barrier); `live`: the thread's wavefront has sites.
-template <int Q>
-__device__ inline void links_blocks_group(const Table& tb, int32_t g, int32_t s, bool live,
-                                          StageLds& lds, int32_t (&j)[Q]) {
-    const StageHdr h = stage_header(tb, g);
-    if (h.nown == 0) {  // the group's records did not fit: global records
-        if (live) links_blocks_wave<Q>(tb, s, j);
-        return;
-    }
-    stage_commit(stage_fetch(tb, h), lds);
-    __syncthreads();
-    if (live) decode_staged<Q>(tb, h.nown, s, lds, j);
+// Gather the pre-collision deviations of the site with row reference own: a reference
+// is the load's 32-bit offset from a uniform base, the direction's row its constant
+// offset.
+template <int Q, int ST, bool SC>
+__device__ inline void refs_gather(const typename Store<ST>::T* __restrict__ A, int64_t base,
+                                   uint32_t own, const uint32_t (&e)[Q], float (&d)[Q]) {
+    using T = typename Store<ST>::T;
+    using C = Codec<Q, ST, SC>;
+    constexpr int kRow = kRowSize<sizeof(T)>;
+    const char* ab = reinterpret_cast<const char*>(A + base);
+    T v[Q];
+    v[0] = *reinterpret_cast<const T*>(ab + own - kRow);
+#pragma unroll
+    for (int i = 1; i < Q; ++i) v[i] = *reinterpret_cast<const T*>(ab + e[i] + (i - 1) * kRow);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) d[i] = C::dec(i, v[i]);
 }
-
-// Links of site s in a kernel whose 256-thread workgroups each cover one group g
-// of four consecutive tiles (s = 256 g + thread).  Every thread of the workgroup
-// calls it; `live`: the thread's wavefront has sites (the others only help stage).
-template <int Q, bool NT>
-__device__ inline void links_group(const Table& tb, int32_t g, int32_t s, bool live,
-                                   StageLds& lds, int32_t (&j)[Q]);
 
 // Wave form of the link decode (all lanes of a wavefront call it); block
-// addressing decodes from the global records here (see links_group).
+// addressing decodes from the global records here.
 template <int Q, bool NT>
 __device__ inline void links_wave(const Table& tb, int32_t s, int32_t (&j)[Q]) {
     if (tb.brec) {
@@ -364,16 +432,6 @@ __device__ inline void links_wave(const Table& tb, int32_t s, int32_t (&j)[Q]) {
     int32_t e0, e1;
     load_codes<Q, NT>(tb, s, c, e0, e1);
     decode_codes<Q>(tb, s, c, e0, e1, j);
-}
-
-template <int Q, bool NT>
-__device__ inline void links_group(const Table& tb, int32_t g, int32_t s, bool live,
-                                   StageLds& lds, int32_t (&j)[Q]) {
-    if (tb.grp) {
-        links_blocks_group<Q>(tb, g, s, live, lds, j);
-        return;
-    }
-    if (live) links_wave<Q, NT>(tb, s, j);
 }
 
 // All links of an arbitrary site (no lane exchange; any lane may call it).
@@ -413,6 +471,17 @@ __device__ inline int32_t ghost_slot(const Ghosts& G, int32_t n, int64_t l) {
 template <int Q>
 __device__ inline int64_t ghost_link(const Ghosts& G, int32_t n, int32_t slot, int i) {
     return G.slot ? (int64_t)G.cell_link[(int64_t)(slot - n) * Q + i] : (int64_t)(slot - n);
+}
+
+// the first iolet link of a site with iolet directions gmask and references e + lo
+template <int Q, int SZ>
+__device__ inline int64_t staged_link(const Ghosts& G, int32_t n, int64_t base,
+                                      const uint32_t (&e)[Q], uint32_t lo, uint32_t gmask) {
+    int64_t l = -1;
+#pragma unroll
+    for (int i = 1; i < Q; ++i)
+        if (l < 0 && (gmask & (1u << i))) l = ghost_link<Q>(G, n, ref_slot<Q, SZ>(e[i] + lo, base), i);
+    return l;
 }
 
 // moments of FP32 deviations: drho = sum d, m = sum c d (constant-folded per lattice)

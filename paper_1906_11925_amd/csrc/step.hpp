@@ -116,6 +116,29 @@ __device__ inline void site_pull(const typename Store<ST>::T* __restrict__ src, 
 #endif
 }
 
+// Post-collision populations e (in storage format) of site s from the pulled ones.
+template <int Q, int ST, bool SC, bool BRINK>
+__device__ inline void site_collide(const float (&d)[Q], float omega,
+                                    const float* __restrict__ alpha, int32_t s,
+                                    typename Store<ST>::T (&e)[Q]) {
+    using C = Codec<Q, ST, SC>;
+    float drho, mx, my, mz;
+    moments<Q>(d, drho, mx, my, mz);
+    const float rho = 1.0f + drho;
+    const float ir = 1.0f / rho;
+    float ux = mx * ir, uy = my * ir, uz = mz * ir;
+    if constexpr (BRINK) {
+        const float a = 1.0f - alpha[s];
+        ux *= a;
+        uy *= a;
+        uz *= a;
+    }
+    float deq[Q];
+    eq_dev<Q>(drho, rho, ux, uy, uz, deq);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) e[i] = C::enc(i, d[i] - omega * (d[i] - deq[i]));
+}
+
 // Collide the pulled populations of site s and store them (and, with the fused
 // ghost epilogue, the incoming populations of its iolet links for time t_next).
 // FOUT: also store the pulled populations themselves into fout, in the site's own
@@ -135,25 +158,13 @@ __device__ inline void site_collide_store(typename Store<ST>::T* __restrict__ ds
     } else {
         (void)fout;
     }
-    float drho, mx, my, mz;
-    moments<Q>(d, drho, mx, my, mz);
-    const float rho = 1.0f + drho;
-    const float ir = 1.0f / rho;
-    float ux = mx * ir, uy = my * ir, uz = mz * ir;
-    if constexpr (BRINK) {
-        const float a = 1.0f - alpha[s];
-        ux *= a;
-        uy *= a;
-        uz *= a;
-    }
-    float deq[Q];
-    eq_dev<Q>(drho, rho, ux, uy, uz, deq);
+    typename Store<ST>::T e[Q];
+    site_collide<Q, ST, SC, BRINK>(d, omega, alpha, s, e);
     float vs[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        const typename Store<ST>::T e = C::enc(i, d[i] - omega * (d[i] - deq[i]));
-        st_pop(dst + tix<Q>(i, s), e);
-        vs[i] = C::dec(i, e);
+        st_pop(dst + tix<Q>(i, s), e[i]);
+        vs[i] = C::dec(i, e[i]);
     }
 #if HLB_FUSE_GHOSTS
     // The iolet links of a site are consecutive in the link list, in direction
@@ -190,15 +201,23 @@ __device__ inline void site_update(const typename Store<ST>::T* __restrict__ src
 }
 
 // Block ids are dealt round-robin to the 8 XCDs (each with its own L2).  With
-// xcd_group = G > 0, every XCD takes G consecutive blocks of a window of 8G
+// groups of G > 0, every XCD takes G consecutive blocks of a window of 8G
 // blocks, so neighbouring sites share an L2 while all XCDs still sweep the
-// Morton order together (and share the last-level cache).
-__device__ inline int32_t xcd_block(int32_t b, int32_t xcd_group) {
-    if (xcd_group > 0) {
-        const int32_t w = 8 * xcd_group;
-        b = (b / w) * w + (b & 7) * xcd_group + (b >> 3) % xcd_group;
+// Morton order together (and share the last-level cache).  code (xcd_code): G, or
+// -1 - log2 G for a power of two, which needs no division.
+__device__ inline int32_t xcd_block(int32_t b, int32_t code) {
+    if (code < 0) {
+        const int32_t sh = -1 - code, w = 8 << sh;
+        return (b & -w) + ((b & 7) << sh) + ((b >> 3) & ((1 << sh) - 1));
+    }
+    if (code > 0) {
+        const int32_t w = 8 * code;
+        b = (b / w) * w + (b & 7) * code + (b >> 3) % code;
     }
     return b;
+}
+inline int32_t xcd_code(int32_t group) {
+    return group > 0 && (group & (group - 1)) == 0 ? -1 - __builtin_ctz((unsigned)group) : group;
 }
 
 // One workgroup (group g of four tiles) of the fused step.  Every thread of the
@@ -208,50 +227,40 @@ __device__ inline void stream_collide_group(const typename Store<ST>::T* __restr
                                             typename Store<ST>::T* __restrict__ dst,
                                             const Table& tb, int32_t n, int32_t g, float omega,
                                             const float* __restrict__ alpha, const Ghosts& G,
-                                            int64_t t_next, StageLds& lds,
+                                            int64_t t_next, StageLds& lds, LinkLds<Q>& links,
                                             typename Store<ST>::T* __restrict__ fout = nullptr) {
+    constexpr int SZ = sizeof(typename Store<ST>::T);
     if (g * kScBlock >= n) return;  // the whole workgroup lies past the end
     const int32_t s = g * kScBlock + (int32_t)threadIdx.x;
     const bool live = (s & ~(kTile - 1)) < n;  // the wavefront's tile has sites
-    // all link decoding, then all population gathers, before any arithmetic
-    int32_t j[Q];
-    links_group<Q, HLB_NT_TABLE != 0>(tb, g, s, live, lds, j);
-    if (!live || s >= n) return;
-    site_update<Q, ST, SC, BRINK, BFL, FOUT>(src, dst, n, omega, alpha, G, t_next, s, j, fout);
-}
-
-// Links of the sites of a workgroup of W tiles (W a multiple of 4) from the
-// staged records of its W/4 groups: every thread takes its share of its group's
-// blob, one barrier, then every wavefront decodes its tile.  Groups whose records
-// did not fit decode from the global records.  Every thread calls it.
-template <int Q, int W, bool WAIT_VM = false>
-__device__ inline void links_tiles(const Table& tb, int32_t T0, int32_t n, StageLds (&lds)[W / 4],
-                                   int32_t (&j)[Q]) {
-    const int wave = (int)threadIdx.x >> kTileShift;
-    const int32_t g = (T0 >> 2) + (wave >> 2);  // this thread's group of four tiles
-    const int32_t s = (T0 << kTileShift) + (int32_t)threadIdx.x;
-    const bool live = (s & ~(kTile - 1)) < n;
-    StageHdr h{0, 0, 0};
-    if (((int64_t)g << 8) < n) {
-        h = stage_header(tb, g);
-        // the group's 256 threads fetch its blob (thread index within the group)
-        const int32_t t = (int32_t)threadIdx.x & (kScBlock - 1);
+    if constexpr (!BFL) {
+        if (tb.grp)
+            stage_links<Q>(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> kTileShift),
+                           (int)threadIdx.x & (kTile - 1), links);
+        const StageHdr h = tb.grp ? stage_header(tb, g) : StageHdr{0, 0, 0, false};
         if (h.nown > 0) {
-            const int row_chunks = (h.nown * kRowBytes + 15) >> 4;
-            if (t < row_chunks + h.nrec)
-                lds[wave >> 2].chunk[t < row_chunks ? t : kStageRowChunks + t - row_chunks] =
-                    tb.gblob[h.off + t];
+            const int64_t base = group_base(tb.wide, 4 * g, Q);
+            stage(tb, h, g, (int)threadIdx.x, lds);
+            lds_loads_done();
+            __syncthreads();
+            if (s >= n) return;
+            const uint32_t own = slot_ref<Q, SZ>(s, (uint32_t)base);
+            uint32_t e[Q];
+            Pulled<Q> P;
+            staged_refs<Q, SZ>(tb, h, (int)threadIdx.x, (uint32_t)base, own, lds, links, e,
+                                P.gmask);
+            refs_gather<Q, ST, SC>(src, base, own, e, P.d);
+            P.gl = P.gmask ? staged_link<Q, SZ>(G, n, base, e, 0u, P.gmask) : -1;
+            site_collide_store<Q, ST, SC, BRINK, FOUT>(dst, n, omega, alpha, G, t_next, s, P, fout);
+            return;
         }
     }
-    // WAIT_VM: the caller issued loads that write LDS directly; they count as vector
-    // memory operations, so wait for every one of them before the barrier
-    if constexpr (WAIT_VM) __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+    // all link decoding, then all population gathers, before any arithmetic
     if (!live) return;
-    if (h.nown > 0)
-        decode_staged<Q>(tb, h.nown, s, lds[wave >> 2], j);
-    else
-        links_blocks_wave<Q>(tb, s, j);
+    int32_t j[Q];
+    links_wave<Q, HLB_NT_TABLE != 0>(tb, s, j);
+    if (s >= n) return;
+    site_update<Q, ST, SC, BRINK, BFL, FOUT>(src, dst, n, omega, alpha, G, t_next, s, j, fout);
 }
 
 // The fused step for a workgroup of W consecutive tiles (64 W threads) that first
@@ -259,8 +268,7 @@ __device__ inline void links_tiles(const Table& tb, int32_t T0, int32_t n, Stage
 // upstream site (or ghost slot) lies in those tiles reads LDS, any other reads
 // global memory, so each wavefront's gathers touch only the lines of tiles outside
 // the workgroup.  Block addressing, halfway walls.  Every thread calls it.  With DMA
-// (FP32 storage) the copy uses loads that write LDS directly; pops must then be
-// 16-byte aligned.
+// the copy uses loads that write LDS directly; pops must then be 16-byte aligned.
 template <int Q, int ST, bool SC, bool BRINK, int W, bool DMA = false, bool FOUT = false>
 __device__ inline void stream_collide_staged(const typename Store<ST>::T* __restrict__ src,
                                              typename Store<ST>::T* __restrict__ dst,
@@ -269,65 +277,75 @@ __device__ inline void stream_collide_staged(const typename Store<ST>::T* __rest
                                              const float* __restrict__ alpha, const Ghosts& G,
                                              int64_t t_next,
                                              typename Store<ST>::T (&pops)[W][Q][kTile],
-                                             StageLds (&lds)[W / 4],
+                                             StageLds (&lds)[W / 4], LinkLds<Q>& links,
                                              typename Store<ST>::T* __restrict__ fout = nullptr) {
     using T = typename Store<ST>::T;
     using C = Codec<Q, ST, SC>;
+    constexpr int SZ = sizeof(T), kRow = kRowSize<SZ>, kTileBytes = Q * kRow;
     if (((int64_t)T0 << kTileShift) >= n) return;
-    const int wave = (int)threadIdx.x >> kTileShift, lane = (int)threadIdx.x & (kTile - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> kTileShift);
+    const int lane = (int)threadIdx.x & (kTile - 1);
     const int32_t staged = min(W, tiles_alloc - T0);  // tiles of the array in this workgroup
-    constexpr bool kDma = DMA && sizeof(T) == 4;
+    stage_links<Q>(wave, lane, links);
     if (wave < staged) {
-        if constexpr (kDma) {
+        if constexpr (DMA) {
             // A tile's Q rows are one contiguous block, in memory as in LDS: copy it
             // with 16 bytes per lane per load, written straight into LDS (no
-            // registers, no LDS store instructions).  The barrier in links_tiles
-            // waits for these loads.
-            constexpr int kBytes = Q * kTile * 4;
-            const char* g = reinterpret_cast<const char*>(src + (int64_t)(T0 + wave) * (Q * kTile));
+            // registers, no LDS store instructions).
+            constexpr int kBytes = kTileBytes;
+            const char* gp = reinterpret_cast<const char*>(src + (int64_t)(T0 + wave) * (Q * kTile));
             char* l = reinterpret_cast<char*>(&pops[wave][0][0]);
 #pragma unroll
             for (int c = 0; c < (kBytes + 1023) / 1024; ++c)
                 if (c * 1024 + lane * 16 < kBytes)
-                    __builtin_amdgcn_global_load_lds(g + c * 1024 + lane * 16, l + c * 1024, 16, 0, 0);
+                    load_lds16(gp + c * 1024 + lane * 16, l + c * 1024);
         } else {
             const int32_t s = ((T0 + wave) << kTileShift) + lane;
 #pragma unroll
             for (int i = 0; i < Q; ++i) pops[wave][i][lane] = src[tix<Q>(i, s)];
         }
     }
-    int32_t j[Q];
-    links_tiles<Q, W, kDma>(tb, T0, n, lds, j);  // holds the barrier after the staging
+    // this thread's group of four tiles; the group's 256 threads stage its records
+    const int32_t g = (T0 >> 2) + (wave >> 2);
+    const int t = (int)threadIdx.x & (kScBlock - 1);
+    StageLds& map = lds[wave >> 2];
+    StageHdr h{0, 0, 0, false};
+    if (((int64_t)g << 8) < n) h = stage_header(tb, g);
+    if (h.nown > 0) stage(tb, h, g, t, map);
+    const int64_t base = group_base(tb.wide, 4 * g, Q);
+    lds_loads_done();
+    __syncthreads();
     const int32_t s = (T0 << kTileShift) + (int32_t)threadIdx.x;
+    if ((s & ~(kTile - 1)) >= n) return;
+    if (h.nown == 0) {
+        int32_t j[Q];
+        links_blocks_wave<Q>(tb, s, j);
+        if (s >= n) return;
+        site_update<Q, ST, SC, BRINK, false, FOUT>(src, dst, n, omega, alpha, G, t_next, s, j, fout);
+        return;
+    }
     if (s >= n) return;
-    const int32_t lo = T0 << kTileShift;
-    const uint32_t span = (uint32_t)staged << kTileShift;
+    const char* sb = reinterpret_cast<const char*>(src + base);
+    const char* pb = reinterpret_cast<const char*>(&pops[0][0][0]);
+    const uint32_t lo = (uint32_t)((int64_t)T0 * (Q * kTile) - base) * SZ;
+    const uint32_t span = (uint32_t)(staged * kTileBytes + kRow);
+    const uint32_t own = (uint32_t)(wave * kTileBytes + kRow + lane * SZ);  // from lo
+    uint32_t e[Q];  // from lo
     Pulled<Q> P;
+    staged_refs<Q, SZ>(tb, h, t, (uint32_t)base + (uint32_t)(lo / SZ), own, map, links, e,
+                        P.gmask);
     P.d[0] = C::dec(0, pops[wave][0][lane]);
+    // LDS first, then the lanes whose source lies outside the workgroup overwrite
+    T v[Q];
 #pragma unroll
-    for (int i = 1; i < Q; ++i) {
-        int dir;
-        int32_t site;
-        link_src(i, j[i], s, dir, site);
-        const uint32_t r = (uint32_t)(site - lo);
-        const T v = r < span ? pops[r >> kTileShift][dir][r & (kTile - 1)] : src[tix<Q>(dir, site)];
-        P.d[i] = C::dec(i, v);
-    }
-    P.gmask = 0;
-    P.gl = -1;
-#if HLB_FUSE_GHOSTS
-    int32_t top = j[1];
+    for (int i = 1; i < Q; ++i)
+        v[i] = *reinterpret_cast<const T*>(pb + (e[i] < span ? e[i] : own) + (i - 1) * kRow);
 #pragma unroll
-    for (int i = 2; i < Q; ++i) top = max(top, j[i]);
-    if (top >= n) {
+    for (int i = 1; i < Q; ++i)
+        if (e[i] >= span) v[i] = *reinterpret_cast<const T*>(sb + (e[i] + lo) + (i - 1) * kRow);
 #pragma unroll
-        for (int i = 1; i < Q; ++i)
-            if (j[i] >= n) {
-                if (P.gl < 0) P.gl = ghost_link<Q>(G, n, j[i], i);
-                P.gmask |= 1u << i;
-            }
-    }
-#endif
+    for (int i = 1; i < Q; ++i) P.d[i] = C::dec(i, v[i]);
+    P.gl = P.gmask ? staged_link<Q, SZ>(G, n, base, e, lo, P.gmask) : -1;
     site_collide_store<Q, ST, SC, BRINK, FOUT>(dst, n, omega, alpha, G, t_next, s, P, fout);
 }
 
