@@ -217,6 +217,9 @@ int hemelb_lb_links(const uint8_t* labels, const int32_t shape[3], const int32_t
  *                          none below 256 four-tile groups)
  *   HEMELB_LDS_DMA=0       make that copy go through registers instead of loads
  *                          that write LDS directly
+ *   HEMELB_FUSE=K,W,T,R    make K (2 to 4) steps per launch in workgroups of up to W tiles
+ *                          and T threads with LDS rows of class R (0 to 2); 0 never
+ *                          (default: lattices of up to 2^18 sites, 80000 with wall_q)
  *   HEMELB_VERBOSE=1       print the time of each setup phase to stderr
  */
 int hemelb_lb_create(hemelb_lb_t* out, const hemelb_lb_desc_t* desc);
@@ -229,8 +232,12 @@ int hemelb_lb_destroy(hemelb_lb_t h);
  * these as site updates) on the handle's stream and return without waiting.
  * Each step is one fused stream+collide launch, whose epilogue also writes the
  * incoming iolet populations of the next step; a separate ghost fill runs only
- * before the first step after create, set_state or set_deviations.  Once per
- * 1024 steps a small kernel tabulates the iolet time series.
+ * before the first step after create, set_state or set_deviations.  On small
+ * lattices one launch makes several steps where nothing asks for them one by one (a
+ * record, kernel timing, a divergence check or the objective's window), with the same
+ * results; a handle of which a call was captured into a graph steps one by one from
+ * then on.  Once per 1024 steps a small kernel
+ * tabulates the iolet time series.
  * Errors: EINVAL (n < 0), EORDER (past the end of a record), ECANCELLED, EDEVICE.
  */
 int hemelb_lb_step(hemelb_lb_t h, int64_t n);

@@ -10,7 +10,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhemelb_lb.so")
 SOURCES = [os.path.join(CSRC, "kernels.hip"), os.path.join(CSRC, "adjoint.hip"),
-           os.path.join(CSRC, "render.hip"), os.path.join(CSRC, "host.cpp")]
+           os.path.join(CSRC, "render.hip"), os.path.join(CSRC, "fuse.hip"),
+           os.path.join(CSRC, "host.cpp")]
 
 
 def hipcc() -> str:
@@ -71,6 +72,7 @@ def sanitized_command(kind, sources, out):
         hipcc(),
         "--offload-arch=gfx950",
         "--offload-host-only",
+        "-DHLB_NO_DEVICE",
         "-O1",
         "-g",
         "-std=c++17",

@@ -20,6 +20,7 @@
 
 #include "../../include/hemelb_lb.h"
 #include "adjoint.hpp"
+#include "fuse.hpp"
 #include "kernels.hpp"
 #include "render.hpp"
 #include <rocprofiler-sdk-roctx/roctx.h>
@@ -221,6 +222,17 @@ struct hemelb_lb {
 
     void* A[2] = {nullptr, nullptr};
     int cur = 0;  // A[cur] holds the current post-collision state
+    // several steps per launch (small lattices): group data, and a third population
+    // buffer for the state before the last step, which the observables re-gather
+    hlb::Fuse fuse{nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0, 0};
+    int32_t* f_hdr = nullptr;
+    uint32_t* f_list = nullptr;
+    uint32_t* f_rows = nullptr;
+    uint16_t* f_frac = nullptr;
+    void* A_prev = nullptr;
+    // a call of this handle was captured: its graph holds the buffers of that moment, so
+    // their roles may no longer change other than step by step, and nothing is fused
+    bool captured = false;
     bool bfl = false;           // interpolated walls present
     int32_t* tbl = nullptr;     // int32 table (when the compact one does not apply)
     uint16_t* t16 = nullptr;    // compact table
@@ -403,7 +415,8 @@ void release(hemelb_lb* h) {
         if (p) (void)hipFree(p);
     for (void* p : h->frec)
         if (p) (void)hipFree(p);
-    void* ptrs[] = {h->A[0],      h->A[1],      h->tbl,        h->g_site,    h->g_dir,
+    void* ptrs[] = {h->A_prev,    h->f_hdr,     h->f_list,     h->f_rows,    h->f_frac,
+                    h->A[0],      h->A[1],      h->tbl,        h->g_site,    h->g_dir,
                     h->t16,       h->toff,      h->tlist,      h->brec,      h->gmask,
                     h->bnbr,      h->tblock,    h->g_slot,     h->gblob,     h->grp,
                     h->g_cell_link, h->is_link,
@@ -904,6 +917,45 @@ int do_step(hemelb_lb* h) {
     return HEMELB_OK;
 }
 
+// Called by every entry point that enqueues work on A: note whether it is captured.
+int note_capture(hemelb_lb* h) {
+    if (h->fuse.steps == 0 || h->captured) return HEMELB_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(h->stream, &cap), "capture status");
+    h->captured = cap != hipStreamCaptureStatusNone;
+    return HEMELB_OK;
+}
+
+// Whether the steps from time t can be made by one launch of the fused kernel: the
+// group data exist and nothing wants the steps one by one (a record, kernel timing, a
+// captured call, a check or the objective within them).
+bool can_fuse(const hemelb_lb* h, int64_t t) {
+    const int64_t K = h->fuse.steps;
+    if (K == 0 || h->captured || h->rec_t0 >= 0 || h->ev_cap > 0 || !hlb::ghosts_fused()) return false;
+    if (h->check_every > 0 && t / h->check_every != (t + K) / h->check_every) return false;
+    return !(h->obj_set && t < h->w1 && t + K > h->w0);
+}
+
+// The next fuse.steps steps in one launch.  keep: the state before the last of them
+// is kept as well, as after single steps (wanted unless another fused launch comes
+// next).
+int do_fused(hemelb_lb* h, bool keep) {
+    const hlb::Layout L = h->layout();
+    void* src = h->A[h->cur];
+    void* dst = h->A[h->cur ^ 1];
+    if (!h->ghosts_ready)
+        HIP_TRY(hlb::launch_ghost_fill(L, h->ghosts(), src, h->t, h->stream), "ghost fill");
+    HIP_TRY(hlb::launch_fused_steps(L, h->ghosts(), h->fuse, src, dst, keep ? h->A_prev : nullptr,
+                                    h->omega, h->alpha, h->t, h->stream),
+            "fused steps");
+    if (keep) std::swap(h->A[h->cur], h->A_prev);
+    h->cur ^= 1;
+    h->t += h->fuse.steps;
+    h->streamed = true;
+    h->ghosts_ready = true;
+    return HEMELB_OK;
+}
+
 int check_flag(hemelb_lb* h) {
     int32_t f = 0;
     HIP_TRY(hipMemcpy(&f, h->flag, sizeof f, hipMemcpyDeviceToHost), "flag readback");
@@ -928,10 +980,208 @@ struct HostPlan {
     std::vector<double> harm;
     std::vector<float> alpha;
     std::vector<int32_t> perm;
+    int fuse_steps = 0, fuse_threads = 0;  // several steps per launch (0: not built)
+    int32_t fuse_lds = 0;
+    int fuse_pitch = 0;
+    std::vector<int32_t> fuse_hdr;
+    std::vector<uint32_t> fuse_list, fuse_rows;
+    std::vector<uint16_t> fuse_frac;
     double addr_bytes = 0;  // addressing data one step reads: the table, or the staged
                             // block records and group entries (plus global records of
                             // groups whose staged copy would not fit) and tile blocks
 };
+
+// Groups of the several-steps-per-launch kernel (see fuse.hpp): `steps` steps per
+// launch, at most `tiles` tiles per group, fewer where the sites around them would not
+// fit a row of LDS.  False, and nothing built, if a single tile does not fit or there
+// would be more than `max_groups` groups.
+bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, int steps, int tiles,
+                int threads, int row, int64_t max_groups, HostPlan& P) {
+    const int q = d->lattice;
+    const int64_t n = d->n_sites;
+    const int elem = d->storage == HEMELB_STORE_F32 ? 4 : 2;
+    const bool bfl = d->wall_q != nullptr;
+    const int words = hlb::fuse_row_words(q, bfl);
+    const int64_t ttiles = (n + hlb::kTile - 1) / hlb::kTile;
+    const int32_t pitch = hlb::fuse_row_bytes(q, row) / elem;  // elements
+    // references and the packed link number of a D3Q15 row must fit
+    if ((n + P.nghost + 2 * hlb::kTile) * q * elem >= ((int64_t)1 << 31) || P.nghost >= (1 << 17))
+        return false;
+    struct Part {  // the groups of one task
+        std::vector<int32_t> hdr;
+        std::vector<uint32_t> list;
+        std::vector<int32_t> site;  // of every local site, as list
+        int32_t rows = 0, nloc = 0;
+        bool fits = true;
+    };
+    const unsigned nt = (unsigned)std::max<int64_t>(1, std::min<int64_t>(worker_count(), n / 1024));
+    std::vector<Part> part(nt);
+    run_tasks(nt, [&](unsigned w) {
+        Part& p = part[w];
+        std::vector<int32_t> site;
+        std::vector<uint8_t> seen(n, 0);
+        int32_t count[hlb::kFuseMaxSteps + 1];
+        // the sites of R_0 .. R_steps of the tiles [a, b)
+        auto grow = [&](int64_t a, int64_t b) {
+            site.clear();
+            for (int64_t m = a * hlb::kTile; m < std::min(n, b * hlb::kTile); ++m) {
+                seen[m] = 1;
+                site.push_back((int32_t)m);
+            }
+            count[0] = (int32_t)site.size();
+            size_t from = 0;
+            for (int k = 1; k <= steps; ++k) {
+                const size_t to = site.size();
+                for (size_t x = from; x < to; ++x) {
+                    const int64_t s = P.order[site[x]];
+                    for (int i = 1; i < q; ++i) {
+                        const int32_t v = d->nbr[s * q + i];
+                        if (v < 0 || seen[P.inv[v]]) continue;
+                        seen[P.inv[v]] = 1;
+                        site.push_back(P.inv[v]);
+                    }
+                }
+                std::sort(site.begin() + to, site.end());  // neighbouring sites in neighbouring lanes
+                from = to;
+                count[k] = (int32_t)site.size();
+            }
+            for (int32_t m : site) seen[m] = 0;
+            // the steps between the first and the last hold one site per thread
+            return count[steps - 1] <= pitch && (steps == 2 || count[steps - 2] <= threads);
+        };
+        const int64_t end = ttiles * (w + 1) / nt;
+        for (int64_t T = ttiles * w / nt; T < end && p.fits;) {
+            int64_t take = std::min<int64_t>(tiles, end - T);
+            while (!(p.fits = grow(T, T + take)) && take > 1) --take;
+            const size_t h = p.hdr.size();
+            p.hdr.resize(h + hlb::kFuseHdr, 0);
+            p.hdr[h] = (int32_t)(T * hlb::kTile);
+            p.hdr[h + 1] = (int32_t)p.site.size();
+            p.hdr[h + 2] = p.rows;
+            for (int k = 0; k <= steps; ++k) p.hdr[h + 4 + k] = count[k];
+            p.rows += count[steps - 1] * (words / 4);
+            p.nloc = std::max(p.nloc, count[steps]);
+            p.site.insert(p.site.end(), site.begin(), site.end());
+            T += take;
+        }
+    });
+    int32_t nloc = 0;
+    int64_t groups = 0;
+    for (const Part& p : part) {
+        if (!p.fits) return false;
+        nloc = std::max(nloc, p.nloc);
+        groups += (int64_t)(p.hdr.size() / hlb::kFuseHdr);
+    }
+    if (groups > max_groups) return false;
+    const int32_t lds = hlb::fuse_lds(q, row, nloc > pitch ? nloc + pitch : nloc);
+    if (lds > hlb::kFuseMaxLds) return false;
+    // wall fractions of the sites that have any, in site order
+    std::vector<int32_t> walls;
+    if (bfl) {
+        walls.assign(n, -1);
+        for (int64_t m = 0; m < n; ++m) {
+            const int64_t s = P.order[m];
+            for (int i = 1; i < q && walls[m] < 0; ++i)
+                if (d->nbr[s * q + i] == HEMELB_LINK_WALL)
+                    walls[m] = (int32_t)(P.fuse_frac.size() / (q - 1));
+            if (walls[m] < 0) continue;
+            for (int i = 1; i < q; ++i)
+                P.fuse_frac.push_back(d->nbr[s * q + i] == HEMELB_LINK_WALL
+                                          ? (uint16_t)wall_code(d->wall_q[s * q + i])
+                                          : (uint16_t)0);
+        }
+        if (P.fuse_frac.empty()) P.fuse_frac.push_back(0);
+    }
+    std::vector<size_t> list0(nt + 1, 0), row0(nt + 1, 0);
+    for (unsigned w = 0; w < nt; ++w) {
+        list0[w + 1] = list0[w] + part[w].site.size();
+        row0[w + 1] = row0[w] + (size_t)part[w].rows;
+    }
+    P.fuse_list.assign(list0[nt], 0u);
+    P.fuse_rows.assign(row0[nt] * 4, 0u);
+    run_tasks(nt, [&](unsigned w) {
+        Part& p = part[w];
+        std::vector<int32_t> local(n, -1);
+        for (size_t k = 0; k < p.site.size(); ++k) {
+            const int64_t m = p.site[k];
+            P.fuse_list[list0[w] + k] =
+                (uint32_t)((m / hlb::kTile * q * hlb::kTile + m % hlb::kTile + hlb::kTile) * elem);
+        }
+        for (size_t h = 0; h < p.hdr.size(); h += hlb::kFuseHdr) {
+            const int32_t* site = p.site.data() + p.hdr[h + 1];
+            const int32_t nrow = p.hdr[h + 4 + steps - 1], all = p.hdr[h + 4 + steps];
+            const int32_t gap = p.hdr[h + 3] = all > pitch ? pitch : 0;
+            for (int32_t x = 0; x < all; ++x) local[site[x]] = x < nrow ? x : x + gap;
+            const size_t base = (row0[w] + (size_t)p.hdr[h + 2]) * 4;
+            for (int32_t x = 0; x < nrow; ++x) {
+                const int64_t m = site[x], s = P.order[m];
+                uint32_t row[12] = {0}, mask = 0;
+                for (int i = 1; i < q; ++i) {
+                    const int32_t v = d->nbr[s * q + i];
+                    int32_t at = pitch + x;
+                    if (v >= 0)
+                        at = pitch + local[P.inv[v]];
+                    else if (v == HEMELB_LINK_WALL)
+                        at = pitch + x + (opp_dir(i) - i) * pitch;
+                    else
+                        mask |= 1u << i;
+                    row[(i - 1) >> 1] |= (uint32_t)(at * elem) << (16 * ((i - 1) & 1));
+                }
+                if (q == 15) {
+                    row[7] = (uint32_t)gbase[m] << 14 | mask >> 1;
+                } else {
+                    row[9] = (uint32_t)gbase[m];
+                    row[10] = mask;
+                }
+                if (bfl) row[q == 15 ? 8 : 11] = (uint32_t)walls[m];
+                for (int c = 0; c < words; ++c)
+                    P.fuse_rows[base + ((size_t)(c / 4) * nrow + x) * 4 + c % 4] = row[c];
+            }
+            for (int32_t x = 0; x < all; ++x) local[site[x]] = -1;
+            p.hdr[h + 1] += (int32_t)list0[w];
+            p.hdr[h + 2] += (int32_t)row0[w];
+        }
+    });
+    for (Part& p : part) P.fuse_hdr.insert(P.fuse_hdr.end(), p.hdr.begin(), p.hdr.end());
+    P.fuse_steps = steps;
+    P.fuse_threads = threads;
+    P.fuse_pitch = row;
+    P.fuse_lds = lds;
+    return true;
+}
+
+// Whether and how steps are fused: for lattices of up to 2^18 sites (80k with
+// interpolated walls), where a launch's latencies and not its bytes are the cost.  Us a
+// step, single / fused:
+//   13k-site pipe, 3 steps, 1 tile a group: D3Q15 8.2 / 4.2 (start of this form 9.0),
+//     D3Q19 9.0 / 4.4; interpolated walls 7.3 / 5.4, 8.4 / 5.8
+//   2 steps, 2 tiles: 24k 8.7 / 5.1, 53k 9.2 / 5.8, 70k 12.3 / 6.3 (D3Q19 14.6 / 7.8,
+//     FP16 12.3 / 6.6); interpolated walls 53k 8.0 / 7.1
+//   2 steps, 4 tiles: 100k 9.9 / 6.6, 120k 9.8 / 7.0 (FP16 9.9 / 6.9); trees 150k
+//     11.4 / 9.5, 230k 13.6 / 12.6
+//   2 steps, 8 tiles: 200k aneurysm 11.5 / 8.7 (FP16 10.4 / 6.5); not above: 300k pipe
+//     15.2 / 14.2, 600k FP16 19.1 / 20.7; interpolated walls 200k 14.6 / 18.6
+// Eight tiles where all groups then run at once (two per compute unit), which takes
+// more than 4 tiles a group from 131k sites on.
+void choose_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, HostPlan& P) {
+    const int64_t n = d->n_sites;
+    const bool narrow = d->storage != HEMELB_STORE_F32;  // rows of LDS hold twice the sites
+    if (const char* e = getenv("HEMELB_FUSE")) {
+        int steps = 0, tiles = 0, threads = 0, row = 0;
+        if (std::sscanf(e, "%d,%d,%d,%d", &steps, &tiles, &threads, &row) == 4 && steps >= 2 &&
+            steps <= hlb::kFuseMaxSteps && tiles >= 1 && tiles <= 64 && threads >= 64 &&
+            threads <= hlb::kFuseMaxThreads && threads % hlb::kTile == 0 && row >= 0 &&
+            row < hlb::kFusePitches)
+            build_fuse(d, gbase, steps, tiles, threads, row, 1 << 30, P);
+        return;
+    }
+    if (n > (d->wall_q ? 80000 : (int64_t)1 << 18)) return;
+    constexpr int64_t all = 1 << 30;
+    if (n <= 16384 && build_fuse(d, gbase, 3, 1, 512, 1, all, P)) return;
+    if (n <= 80000 && build_fuse(d, gbase, 2, 2, 512, 0, all, P)) return;
+    if (n > 131072 && build_fuse(d, gbase, 2, 8, 1024, narrow ? 0 : 2, 512, P)) return;
+    build_fuse(d, gbase, 2, 4, 768, narrow ? 0 : 1, all, P);
+}
 
 // Validate d and build the host side of its layout (no device work).
 int make_plan(const hemelb_lb_desc_t* d, HostPlan& P, Progress& prog) {
@@ -1008,16 +1258,22 @@ int make_plan(const hemelb_lb_desc_t* d, HostPlan& P, Progress& prog) {
     bool blocks = false;
     const bool try_blocks = (d->flags & HEMELB_FLAG_BLOCKS) ||
                             !(d->flags & (HEMELB_FLAG_TABLE16 | HEMELB_FLAG_TABLE32));
-    if (try_blocks && n > 0) {
-        if (!d->coords)
+    // the groups of several steps per launch are built beside it
+    run_tasks(n > 0 ? 2 : 0, [&](unsigned k) {
+        if (k == 1) {
+            choose_fuse(d, gbase, P);
+        } else if (!try_blocks) {
+            return;
+        } else if (!d->coords) {
             P.bp.why = "it needs site coordinates";
-        else if (d->wall_q)
+        } else if (d->wall_q) {
             P.bp.why = "interpolated walls need the neighbour table";
-        else
+        } else {
             blocks = build_blocks(d, lat, P.order, P.inv, gbase, P.gsite, P.gdir, P.giol, P.ttiles,
                                   P.bp);
-    }
-    if (try_blocks && n > 0) prog("block addressing");
+        }
+    });
+    if (n > 0) prog("block addressing, fused steps");
     if ((d->flags & HEMELB_FLAG_BLOCKS) && n > 0 && !blocks)
         return fail(HEMELB_EINVAL, "block addressing does not apply: %s", P.bp.why.c_str());
     const int64_t ghost_slots = blocks ? P.bp.ncells : P.nghost;
@@ -1183,6 +1439,10 @@ int64_t planned_device_bytes(const HostPlan& P, int q, size_t elem) {
     b += (int64_t)(P.dio.size() * sizeof(hlb::DevIolet) + P.harm.size() * 8);
     b += (int64_t)(P.perm.size() * 4 + P.nrm.size() * 4 + P.alpha.size() * 4);
     b += hlb::totals_parts(P.n) * 4 * 8 + 4 * 8 + 4;
+    if (P.fuse_steps > 0)
+        b += (int64_t)q * P.slots * (int64_t)elem +
+             (int64_t)(P.fuse_hdr.size() + P.fuse_list.size() + P.fuse_rows.size()) * 4 +
+             (int64_t)P.fuse_frac.size() * 2;
     return b;
 }
 
@@ -1622,6 +1882,30 @@ static int init_handle(hemelb_lb* h, hemelb_lb_t* out, const hemelb_lb_desc_t* d
     } else {
         TRY(dev_upload(h, &h->tbl, P.tbl, "neighbour table"));
     }
+    if (P.fuse_steps > 0) {
+        void* p = nullptr;
+        const hipError_t e = hipMalloc(&p, popbytes);
+        if (e != hipSuccess) {
+            release(h);
+            return hip_fail(e, "population buffer");
+        }
+        h->A_prev = p;
+        h->device_bytes += (int64_t)popbytes;
+        TRY(dev_upload(h, &h->f_hdr, P.fuse_hdr, "step groups"));
+        TRY(dev_upload(h, &h->f_list, P.fuse_list, "step group sites"));
+        TRY(dev_upload(h, &h->f_rows, P.fuse_rows, "step group rows"));
+        TRY(dev_upload(h, &h->f_frac, P.fuse_frac, "step group walls"));
+        h->fuse = hlb::Fuse{h->f_hdr, h->f_list, reinterpret_cast<const uint4*>(h->f_rows), h->f_frac,
+                            (int32_t)(P.fuse_hdr.size() / hlb::kFuseHdr), P.fuse_steps,
+                            P.fuse_threads, P.fuse_pitch, P.fuse_lds};
+        for (const bool brink : {false, true}) {
+            const hipError_t f = hlb::fuse_prepare(h->layout(), h->fuse, brink);
+            if (f != hipSuccess) {
+                release(h);
+                return hip_fail(f, "several steps per launch");
+            }
+        }
+    }
     TRY(dev_upload(h, &h->g_site, P.gsite, "ghost sites"));
     TRY(dev_upload(h, &h->g_dir, P.gdir, "ghost dirs"));
     TRY(dev_upload(h, &h->g_iolet, P.giol, "ghost iolets"));
@@ -1644,8 +1928,9 @@ static int init_handle(hemelb_lb* h, hemelb_lb_t* out, const hemelb_lb_desc_t* d
         }
     }
     const hlb::Layout L = h->layout();
-    for (int b = 0; b < 2; ++b) {
-        hipError_t e = hlb::launch_zero(L, h->A[b], h->stream);
+    for (void* p : {h->A[0], h->A[1], h->A_prev}) {
+        if (!p) continue;
+        hipError_t e = hlb::launch_zero(L, p, h->stream);
         if (e != hipSuccess) {
             release(h);
             return hip_fail(e, "initial state");
@@ -1705,14 +1990,33 @@ int hemelb_lb_step(hemelb_lb_t h, int64_t n) {
                     (long long)h->t);
     HIP_TRY(hipSetDevice(h->device), "set device");
     constexpr int64_t kBatch = 1024;  // steps per table of iolet values
-    for (int64_t k = 0; k < n; ++k) {
-        if (h->cancel.exchange(false))
+    int rc;
+    if ((rc = note_capture(h))) return rc;
+    const int64_t K = h->fuse.steps;
+    int64_t filled = 0;  // steps of this call whose iolet values are tabulated
+    bool kept = true;    // the state before the last step is at hand
+    for (int64_t k = 0; k < n;) {
+        if (h->cancel.exchange(false)) {
+            if (!kept) {
+                if ((rc = do_step(h))) return rc;
+                ++k;
+            }
             return fail(HEMELB_ECANCELLED, "cancelled after %lld of %lld steps", (long long)k,
                         (long long)n);
-        int rc;
-        if (k % kBatch == 0 && (rc = fill_series(h, h->t, std::min(kBatch, n - k) + 1))) return rc;
-        rc = do_step(h);
-        if (rc) return rc;
+        }
+        if (k == filled) {
+            filled = std::min(k + kBatch, n);
+            if ((rc = fill_series(h, h->t, filled - k + 1))) return rc;
+        }
+        if (k + K <= filled && can_fuse(h, h->t)) {
+            kept = k + 2 * K > filled || !can_fuse(h, h->t + K);
+            if ((rc = do_fused(h, kept))) return rc;
+            k += K;
+        } else {
+            kept = true;
+            if ((rc = do_step(h))) return rc;
+            ++k;
+        }
     }
     return HEMELB_OK;
 }
@@ -1747,6 +2051,7 @@ int hemelb_lb_set_stream(hemelb_lb_t h, void* stream) {
 int hemelb_lb_observables(hemelb_lb_t h, float* p, float* u, float* wss) {
     const Range range("hemelb_lb_observables");
     if (!h) return fail(HEMELB_EINVAL, "NULL handle");
+    if (int rc = note_capture(h)) return rc;
     const void* A = h->streamed ? h->A[h->cur ^ 1] : h->A[h->cur];
     HIP_TRY(hlb::launch_observables(h->layout(), A, h->streamed ? 1 : 0, h->omega, h->perm,
                                     h->normal, p, u, wss, h->stream),
@@ -1773,11 +2078,13 @@ int hemelb_lb_totals_noalloc(hemelb_lb_t h, double* out) {
         return fail(HEMELB_EINVAL, "%lld reduction blocks exceed the scratch of %lld",
                     (long long)hlb::totals_parts(h->n), (long long)hlb::totals_scratch_parts());
     HIP_TRY(hipSetDevice(h->device), "set device");
+    if (int rc = note_capture(h)) return rc;
     HIP_TRY(hlb::launch_totals_noalloc(h->layout(), h->A[h->cur], out, h->stream), "totals");
     return HEMELB_OK;
 }
 
 static int state_io(hemelb_lb_t h, void* ext, int mode) {
+    if (int rc = note_capture(h)) return rc;
     HIP_TRY(hlb::launch_state(h->layout(), h->A[h->cur], ext, h->perm, mode, h->stream), "state");
     // a state written by the caller starts a new history: a divergence seen
     // before it no longer applies (a fill kernel, not a memset, so that a
