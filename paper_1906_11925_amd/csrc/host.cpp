@@ -263,6 +263,7 @@ struct hemelb_lb {
     int64_t vals_t0 = 0;
     int32_t basis_stride = 0;   // Fourier basis doubles per (step, iolet): 2 x the most harmonics
     int32_t* perm = nullptr;  // Morton index -> caller index (null: identity)
+    uint16_t* xloc = nullptr;  // caller order within chunks of sites (null: identity)
     float* normal = nullptr;  // [3][n] Morton order
     float* alpha = nullptr;
     double* partial = nullptr;
@@ -364,7 +365,7 @@ struct hemelb_lb {
                            hlb::Table{tbl, t16, toff, tlist, brec, gmask, bnbr, tblock,
                                       reinterpret_cast<const uint4*>(gblob), grp, nfluid, nblocks,
                                       (int32_t)n, wide},
-                           bfl, stage_tiles, lds_dma};
+                           bfl, stage_tiles, lds_dma, xloc};
     }
     hlb::Ghosts ghosts() const {
         return hlb::Ghosts{nghost,  g_slot,   g_cell_link, g_site,  g_dir,   g_iolet,
@@ -420,7 +421,7 @@ void release(hemelb_lb* h) {
                     h->t16,       h->toff,      h->tlist,      h->brec,      h->gmask,
                     h->bnbr,      h->tblock,    h->g_slot,     h->gblob,     h->grp,
                     h->g_cell_link, h->is_link,
-                    h->g_iolet,   h->g_coef,    h->d_iolets,   h->d_harm,    h->perm,
+                    h->g_iolet,   h->g_coef,    h->d_iolets,   h->d_harm,    h->perm,      h->xloc,
                     h->normal,    h->alpha,     h->partial,    h->tot,       h->flag,
                     h->d_out_links, h->d_dome,  h->d_wss_w,    h->d_qtape,   h->d_wtape,
                     h->d_opart,
@@ -980,6 +981,7 @@ struct HostPlan {
     std::vector<double> harm;
     std::vector<float> alpha;
     std::vector<int32_t> perm;
+    std::vector<uint16_t> xloc;
     int fuse_steps = 0, fuse_threads = 0;  // several steps per launch (0: not built)
     int32_t fuse_lds = 0;
     int fuse_pitch = 0;
@@ -1418,7 +1420,21 @@ int make_plan(const hemelb_lb_desc_t* d, HostPlan& P, Progress& prog) {
         for (int hh = 0; hh < io.n_harm; ++hh) P.harm.push_back(io.cos_k[hh]);
         for (int hh = 0; hh < io.n_harm; ++hh) P.harm.push_back(io.sin_k[hh]);
     }
-    if (d->coords) P.perm = P.order;
+    if (d->coords) {
+        P.perm = P.order;
+        P.xloc.resize(n);
+        const int64_t chunks = (n + hlb::kChunk - 1) / hlb::kChunk;
+        const unsigned nt = (unsigned)std::min<int64_t>(worker_count(), std::max<int64_t>(1, chunks / 8));
+        run_tasks(nt, [&](unsigned w) {
+            for (int64_t c = chunks * w / nt; c < chunks * (w + 1) / nt; ++c) {
+                const int64_t lo = c * hlb::kChunk, hi = std::min(n, lo + hlb::kChunk);
+                std::iota(P.xloc.begin() + lo, P.xloc.begin() + hi, (uint16_t)0);
+                std::sort(P.xloc.begin() + lo, P.xloc.begin() + hi, [&](uint16_t x, uint16_t y) {
+                    return P.order[lo + x] < P.order[lo + y];
+                });
+            }
+        });
+    }
     if (d->alpha) {
         P.alpha.resize(n);
         for (int64_t m = 0; m < n; ++m) P.alpha[m] = d->alpha[P.order[m]];
@@ -1437,7 +1453,7 @@ int64_t planned_device_bytes(const HostPlan& P, int q, size_t elem) {
     b += (int64_t)(P.tbl.size() * 4 + P.t16.size() * 2 + P.toff.size() * 4 + P.tlist.size() * 4);
     b += (int64_t)(P.gsite.size() * 4 + P.gdir.size() + P.giol.size() + P.gcoef.size() * 4);
     b += (int64_t)(P.dio.size() * sizeof(hlb::DevIolet) + P.harm.size() * 8);
-    b += (int64_t)(P.perm.size() * 4 + P.nrm.size() * 4 + P.alpha.size() * 4);
+    b += (int64_t)(P.perm.size() * 4 + P.xloc.size() * 2 + P.nrm.size() * 4 + P.alpha.size() * 4);
     b += hlb::totals_parts(P.n) * 4 * 8 + 4 * 8 + 4;
     if (P.fuse_steps > 0)
         b += (int64_t)q * P.slots * (int64_t)elem +
@@ -1913,6 +1929,7 @@ static int init_handle(hemelb_lb* h, hemelb_lb_t* out, const hemelb_lb_desc_t* d
     TRY(dev_upload(h, &h->d_iolets, P.dio, "iolets"));
     TRY(dev_upload(h, &h->d_harm, P.harm, "harmonics"));
     TRY(dev_upload(h, &h->perm, P.perm, "permutation"));
+    TRY(dev_upload(h, &h->xloc, P.xloc, "caller order"));
     TRY(dev_upload(h, &h->normal, P.nrm, "normals"));
     TRY(dev_upload(h, &h->alpha, P.alpha, "alpha"));
     h->nparts = hlb::totals_parts(n);

@@ -129,89 +129,145 @@ __global__ __launch_bounds__(kBlock) void k_ghost_fill(typename Store<ST>::T* __
 // ---------------------------------------------------------------------------
 // observables: pressure deviation, velocity, wall shear stress
 // ---------------------------------------------------------------------------
-template <int Q, int ST, bool SC>
-__global__ __launch_bounds__(kBlock) void k_observables(
-    const typename Store<ST>::T* __restrict__ A, Table tb, int32_t n,
-    int32_t streamed, float omega, const int32_t* __restrict__ perm,
-    const float* __restrict__ normal, float* __restrict__ p, float* __restrict__ u,
-    float* __restrict__ wss) {
+// Bound by requests between L1 and L2, its stores more than its gathers as long as they
+// went out a block's z-run at a time (16 bytes).  ORDER: a workgroup takes a chunk of
+// sites and puts the results into the caller's order in LDS before
+// it stores them (5.6M sites, with the site order of the step before it: FP32 214 -> 184
+// us, FP16 178 -> 152 us; 20.8M sites 833 -> 590 us; two passes of 512 threads took 221
+// and 185 us; the bound on registers keeps two workgroups on a compute unit).  Otherwise
+// one group, stored as it
+// lies: small lattices, where the few large workgroups leave the chip idle, and D3Q19,
+// whose registers do not fit the bound (5.6M sites FP16: 184 us, in order 219 us).
+constexpr int kObsThreads = kChunk;
+
+template <int Q, int ST, bool SC, bool ORDER>
+__global__ __launch_bounds__(ORDER ? kObsThreads : kBlock, ORDER ? 8 : 4) void k_observables(
+    const typename Store<ST>::T* __restrict__ A, Table tb, int32_t n, int32_t streamed,
+    int32_t xcd_group, float omega, const int32_t* __restrict__ perm,
+    const uint16_t* __restrict__ xloc, const float* __restrict__ normal, float* __restrict__ p,
+    float* __restrict__ u, float* __restrict__ wss) {
     using C = Codec<Q, ST, SC>;
     using Lt = Lat<Q>;
-    static_assert(kBlock == 4 * kTile, "a workgroup covers one group of four tiles");
-    __shared__ StageLds lds;
+    using T = typename Store<ST>::T;
+    constexpr int SZ = sizeof(T), kThreads = ORDER ? kObsThreads : kBlock,
+                  kSites = ORDER ? kChunk : kBlock;
+    static_assert(kBlock == 4 * kTile, "a group is four tiles");
+    __shared__ StageLds lds[kThreads / kBlock];
     __shared__ LinkLds<Q> links;
-    const int32_t g = blockIdx.x;
-    const int32_t s = g * kBlock + threadIdx.x;
-    const bool live = (s & ~(kTile - 1)) < n;
-    float d[Q];
-    if (streamed && tb.grp)
-        stage_links<Q>(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> kTileShift),
-                       (int)threadIdx.x & (kTile - 1), links);
-    const StageHdr h = streamed && tb.grp ? stage_header(tb, g) : StageHdr{0, 0, 0, false};
-    if (h.nown > 0) {
-        constexpr int SZ = sizeof(typename Store<ST>::T);
-        const int64_t base = group_base(tb.wide, 4 * g, Q);
-        stage(tb, h, g, (int)threadIdx.x, lds);
+    __shared__ float out[ORDER ? 5 : 1][ORDER ? kChunk : 1];
+    const int32_t first = xcd_block((int32_t)blockIdx.x, xcd_group) * kSites;
+    if (first >= n) return;  // the whole workgroup lies past the end
+    const int tid = (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> kTileShift);
+    const int t = tid & (kBlock - 1);
+    const bool blocks = streamed && tb.grp;
+    if (blocks) stage_links<Q>(wave, tid & (kTile - 1), links);
+#pragma unroll 1
+    for (int k0 = 0; k0 < kSites; k0 += kThreads) {
+    const int32_t s = first + k0 + tid, g = (first + k0) / kBlock + (wave >> 2);
+    const bool live = (s & ~(kTile - 1)) < n, mine = s < n;
+    StageLds& group = lds[wave >> 2];
+    StageHdr h{0, 0, 0, false};
+    if (blocks) {
+        if (k0 > 0) __syncthreads();  // the records before are done with
+        if ((int64_t)g * kBlock < n) h = stage_header(tb, g);
+        if (h.nown > 0) stage(tb, h, g, t, group);
         lds_loads_done();
         __syncthreads();
-        if (s >= n) return;
-        const uint32_t own = slot_ref<Q, SZ>(s, (uint32_t)base);
-        uint32_t e[Q], gmask;
-        staged_refs<Q, SZ>(tb, h, (int)threadIdx.x, (uint32_t)base, own, lds, links, e, gmask);
-        refs_gather<Q, ST, SC>(A, base, own, e, d);
+    }
+    float d[Q];
+    if (h.nown > 0) {
+        if (mine) {
+            const int64_t base = group_base(tb.wide, 4 * g, Q);
+            const uint32_t own = slot_ref<Q, SZ>(s, (uint32_t)base);
+            uint32_t e[Q], gmask;
+            staged_refs<Q, SZ>(tb, h, t, (uint32_t)base, own, group, links, e, gmask);
+            refs_gather<Q, ST, SC>(A, base, own, e, d);
+        }
     } else {
         int32_t j[Q];
         if (streamed && live) links_wave<Q, false>(tb, s, j);
-        if (s >= n) return;
-        d[0] = C::dec(0, A[tix<Q>(0, s)]);
+        if (mine) {
+            d[0] = C::dec(0, A[tix<Q>(0, s)]);
 #pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            int dir = i;
-            int32_t site = s;
-            if (streamed) link_src(i, j[i], s, dir, site);
-            d[i] = C::dec(i, A[tix<Q>(dir, site)]);
+            for (int i = 1; i < Q; ++i) {
+                int dir = i;
+                int32_t site = s;
+                if (streamed) link_src(i, j[i], s, dir, site);
+                d[i] = C::dec(i, A[tix<Q>(dir, site)]);
+            }
+            if (streamed) apply_bfl<Q, ST, SC>(A, s, n, j, d);
         }
-        if (streamed) apply_bfl<Q, ST, SC>(A, s, n, j, d);
     }
-    float drho, mx, my, mz;
-    moments<Q>(d, drho, mx, my, mz);
-    const float rho = 1.0f + drho;
-    const float ir = 1.0f / rho;
-    const float ux = mx * ir, uy = my * ir, uz = mz * ir;
-    const int32_t o = perm ? perm[s] : s;
-    if (p) p[o] = drho * (1.0f / 3.0f);
-    if (u) {
-        u[3 * (int64_t)o + 0] = ux;
-        u[3 * (int64_t)o + 1] = uy;
-        u[3 * (int64_t)o + 2] = uz;
-    }
-    if (!wss) return;
-    const float nx = normal[s], ny = normal[n + s], nz = normal[2 * (int64_t)n + s];
-    if (nx == 0.f && ny == 0.f && nz == 0.f) {
-        wss[o] = 0.f;
-        return;
-    }
-    float deq[Q];
-    eq_dev<Q>(drho, rho, ux, uy, uz, deq);
-    float pxx = 0, pyy = 0, pzz = 0, pxy = 0, pxz = 0, pyz = 0;
+    float op = 0.f, ux = 0.f, uy = 0.f, uz = 0.f, ow = 0.f;
+    if (mine) {
+        float drho, mx, my, mz;
+        moments<Q>(d, drho, mx, my, mz);
+        const float rho = 1.0f + drho;
+        const float ir = 1.0f / rho;
+        ux = mx * ir;
+        uy = my * ir;
+        uz = mz * ir;
+        op = drho * (1.0f / 3.0f);
+        const float nx = wss ? normal[s] : 0.f, ny = wss ? normal[n + s] : 0.f,
+                    nz = wss ? normal[2 * (int64_t)n + s] : 0.f;
+        if (nx != 0.f || ny != 0.f || nz != 0.f) {
+            float deq[Q];
+            eq_dev<Q>(drho, rho, ux, uy, uz, deq);
+            float pxx = 0, pyy = 0, pzz = 0, pxy = 0, pxz = 0, pyz = 0;
 #pragma unroll
-    for (int i = 1; i < Q; ++i) {
-        const float e = d[i] - deq[i];
-        const float cx = Lt::cx[i], cy = Lt::cy[i], cz = Lt::cz[i];
-        if (Lt::cx[i]) pxx += e;
-        if (Lt::cy[i]) pyy += e;
-        if (Lt::cz[i]) pzz += e;
-        if (Lt::cx[i] && Lt::cy[i]) pxy += cx * cy * e;
-        if (Lt::cx[i] && Lt::cz[i]) pxz += cx * cz * e;
-        if (Lt::cy[i] && Lt::cz[i]) pyz += cy * cz * e;
+            for (int i = 1; i < Q; ++i) {
+                const float e = d[i] - deq[i];
+                const float cx = Lt::cx[i], cy = Lt::cy[i], cz = Lt::cz[i];
+                if (Lt::cx[i]) pxx += e;
+                if (Lt::cy[i]) pyy += e;
+                if (Lt::cz[i]) pzz += e;
+                if (Lt::cx[i] && Lt::cy[i]) pxy += cx * cy * e;
+                if (Lt::cx[i] && Lt::cz[i]) pxz += cx * cz * e;
+                if (Lt::cy[i] && Lt::cz[i]) pyz += cy * cz * e;
+            }
+            const float k = -(1.0f - 0.5f * omega);
+            const float sx = k * (pxx * nx + pxy * ny + pxz * nz);
+            const float sy = k * (pxy * nx + pyy * ny + pyz * nz);
+            const float sz = k * (pxz * nx + pyz * ny + pzz * nz);
+            const float nsn = sx * nx + sy * ny + sz * nz;
+            const float tx = sx - nsn * nx, ty = sy - nsn * ny, tz = sz - nsn * nz;
+            ow = sqrtf(tx * tx + ty * ty + tz * tz);
+        }
     }
-    const float k = -(1.0f - 0.5f * omega);
-    const float sx = k * (pxx * nx + pxy * ny + pxz * nz);
-    const float sy = k * (pxy * nx + pyy * ny + pyz * nz);
-    const float sz = k * (pxz * nx + pyz * ny + pzz * nz);
-    const float nsn = sx * nx + sy * ny + sz * nz;
-    const float tx = sx - nsn * nx, ty = sy - nsn * ny, tz = sz - nsn * nz;
-    wss[o] = sqrtf(tx * tx + ty * ty + tz * tz);
+    if constexpr (ORDER) {
+        out[0][k0 + tid] = op;
+        out[1][k0 + tid] = ux;
+        out[2][k0 + tid] = uy;
+        out[3][k0 + tid] = uz;
+        out[4][k0 + tid] = ow;
+    } else if (mine) {
+        const int32_t o = perm ? perm[s] : s;
+        if (p) p[o] = op;
+        if (u) {
+            float* const uo = u + 3 * (int64_t)o;
+            uo[0] = ux;
+            uo[1] = uy;
+            uo[2] = uz;
+        }
+        if (wss) wss[o] = ow;
+    }
+    }
+    if constexpr (ORDER) {
+        __syncthreads();
+        for (int k = tid; k < kChunk && first + k < n; k += kThreads) {
+            const int local = xloc[first + k];
+            const int32_t o = perm[first + local];
+            if (p) p[o] = out[0][local];
+            if (u) {
+                float* const uo = u + 3 * (int64_t)o;
+                uo[0] = out[1][local];
+                uo[1] = out[2][local];
+                uo[2] = out[3][local];
+            }
+            if (wss) wss[o] = out[4][local];
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -294,23 +350,53 @@ __global__ __launch_bounds__(kBlock) void k_totals_final(const double* __restric
 // ---------------------------------------------------------------------------
 // state transfer between the internal (Morton, tiled) and caller layouts
 // ---------------------------------------------------------------------------
+// One workgroup moves one chunk of sites, all directions.  On the caller's side thread k
+// takes the chunk's k-th site in the caller's order, so its accesses are whole pieces of
+// the caller's rows; reading the internal side that way stays within the L1, writing it
+// goes through LDS.
 template <int Q, int ST, bool SC>
-__global__ __launch_bounds__(kBlock) void k_state(typename Store<ST>::T* __restrict__ A,
+__global__ __launch_bounds__(kChunk) void k_state(typename Store<ST>::T* __restrict__ A,
                                                    void* __restrict__ ext,
-                                                   const int32_t* __restrict__ perm, int32_t n,
-                                                   int mode) {
+                                                   const int32_t* __restrict__ perm,
+                                                   const uint16_t* __restrict__ xloc, int32_t n,
+                                                   int32_t xcd_group, int mode) {
     using C = Codec<Q, ST, SC>;
     using T = typename Store<ST>::T;
-    const int32_t s = blockIdx.x * kBlock + threadIdx.x;
-    const int i = blockIdx.y;
-    if (s >= n) return;
-    const int64_t e = (int64_t)i * n + (perm ? perm[s] : s);
-    const int64_t a = tix<Q>(i, s);
-    switch (mode) {
-        case 0: static_cast<T*>(ext)[e] = A[a]; break;
-        case 1: A[a] = static_cast<const T*>(ext)[e]; break;
-        case 2: static_cast<float*>(ext)[e] = C::dec(i, A[a]); break;
-        default: A[a] = C::enc(i, static_cast<const float*>(ext)[e]); break;
+    constexpr int kRows = 5;
+    __shared__ T buf[kRows][kChunk];
+    const int32_t first = xcd_block((int32_t)blockIdx.x, xcd_group) * kChunk;
+    if (first >= n) return;
+    const int32_t s = first + (int32_t)threadIdx.x;
+    const bool mine = s < n;
+    const int local = mine && xloc ? xloc[s] : (int)threadIdx.x;
+    const int32_t o = mine && perm ? perm[first + local] : s;
+    if (mode == 0 || mode == 2) {
+        if (!mine) return;
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const T v = A[tix<Q>(i, first + local)];
+            const int64_t e = (int64_t)i * n + o;
+            if (mode == 0)
+                static_cast<T*>(ext)[e] = v;
+            else
+                static_cast<float*>(ext)[e] = C::dec(i, v);
+        }
+        return;
+    }
+#pragma unroll
+    for (int i0 = 0; i0 < Q; i0 += kRows) {
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+            if (i0 + r < Q && mine) {
+                const int64_t e = (int64_t)(i0 + r) * n + o;
+                buf[r][local] = mode == 1 ? static_cast<const T*>(ext)[e]
+                                          : C::enc(i0 + r, static_cast<const float*>(ext)[e]);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+            if (i0 + r < Q && mine) A[tix<Q>(i0 + r, s)] = buf[r][threadIdx.x];
+        __syncthreads();
     }
 }
 
@@ -426,6 +512,19 @@ hipError_t launch_stream_collide(const Layout& L, const Ghosts& G, const void* s
     });
 }
 
+// Workgroups of one chunk; consecutive chunks on one XCD, whose L2 then joins the pieces
+// of the caller's lines that two chunks share.
+constexpr int kChunkXcd = 16;
+// smallest lattice whose observables' workgroups are grouped by XCD and, D3Q15, put into
+// the caller's order chunk by chunk (1.6M sites 67 -> 43 us; 200k 12.0 as they lie)
+constexpr int64_t kOrderSites = (int64_t)1 << 18;
+constexpr int kObsXcd = 16;
+
+static unsigned chunk_grid(int64_t n) {
+    const int64_t nb = (n + kChunk - 1) / kChunk;
+    return (unsigned)((nb + 8 * kChunkXcd - 1) / (8 * kChunkXcd) * (8 * kChunkXcd));
+}
+
 hipError_t launch_observables(const Layout& L, const void* A, int streamed, float omega,
                               const int32_t* perm, const float* normal, float* p, float* u,
                               float* wss, hipStream_t s) {
@@ -433,9 +532,20 @@ hipError_t launch_observables(const Layout& L, const void* A, int streamed, floa
     return dispatch(L.q, L.storage, L.scaled, [&](auto tag) {
         using Tg = decltype(tag);
         using T = typename Store<Tg::ST>::T;
-        k_observables<Tg::Q, Tg::ST, Tg::SC><<<blocks_for(L.n), kBlock, 0, s>>>(
-            static_cast<const T*>(A), L.tb, (int32_t)L.n, streamed, omega, perm, normal, p, u,
-            wss);
+        auto go = [&](auto kernel, unsigned grid, int threads, int32_t xcd) {
+            kernel<<<grid, threads, 0, s>>>(static_cast<const T*>(A), L.tb, (int32_t)L.n, streamed, xcd,
+                                            omega, perm, L.xloc, normal, p, u, wss);
+        };
+        const bool large = L.n >= kOrderSites;
+        if constexpr (Tg::Q == 15)
+            if (large && perm && L.xloc) {
+                go(k_observables<Tg::Q, Tg::ST, Tg::SC, true>, chunk_grid(L.n), kObsThreads,
+                   xcd_code(kChunkXcd));
+                return hipGetLastError();
+            }
+        const unsigned per = 8 * kObsXcd, nb = blocks_for(L.n);
+        go(k_observables<Tg::Q, Tg::ST, Tg::SC, false>, large ? (nb + per - 1) / per * per : nb, kBlock,
+           large ? xcd_code(kObsXcd) : 0);
         return hipGetLastError();
     });
 }
@@ -501,9 +611,8 @@ hipError_t launch_state(const Layout& L, void* A, void* ext, const int32_t* perm
     return dispatch(L.q, L.storage, L.scaled, [&](auto tag) {
         using Tg = decltype(tag);
         using T = typename Store<Tg::ST>::T;
-        dim3 grid(blocks_for(L.n), (unsigned)Tg::Q);
-        k_state<Tg::Q, Tg::ST, Tg::SC><<<grid, kBlock, 0, s>>>(static_cast<T*>(A), ext, perm,
-                                                                (int32_t)L.n, mode);
+        k_state<Tg::Q, Tg::ST, Tg::SC><<<chunk_grid(L.n), kChunk, 0, s>>>(
+            static_cast<T*>(A), ext, perm, L.xloc, (int32_t)L.n, xcd_code(kChunkXcd), mode);
         return hipGetLastError();
     });
 }

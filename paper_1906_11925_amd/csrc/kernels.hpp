@@ -110,9 +110,17 @@ struct Layout {
     // with block addressing and halfway walls: workgroups of this many tiles (4, 8
     // or 16) copy their own populations into LDS first (0: four tiles, no copy)
     int stage_tiles;
-    // FP32 staging copies with loads that write LDS directly
+    // staging copies with loads that write LDS directly
     bool lds_dma;
+    // caller order within each chunk of kChunk sites: the chunk's k-th site in the
+    // caller's order is its site xloc[chunk * kChunk + k] (null: internal order)
+    const uint16_t* xloc;
 };
+
+// Sites whose outputs a workgroup puts into the caller's order before it stores them.
+// 1024 consecutive sites cover 16 sites along z in a wide vessel, so that a store takes
+// whole 64-byte pieces of the caller's arrays instead of a block's 16 bytes.
+constexpr int kChunk = 1024;
 
 // Iolet links, sorted by site then direction.  Link l's incoming population lives
 // in direction dir[l] of slot slot[l] (null: slot n + l, one slot per link, the
