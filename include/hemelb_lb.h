@@ -209,8 +209,9 @@ int hemelb_lb_links(const uint8_t* labels, const int32_t shape[3], const int32_t
  *
  * Launch-shape settings, read from the environment when a handle is created (none
  * changes any result bit; each exists to compare kernel forms):
- *   HEMELB_XCD_GROUP=G     consecutive workgroups given to one XCD (default 16; 0
- *                          leaves the hardware's round-robin)
+ *   HEMELB_XCD_GROUP=G     consecutive workgroups given to one XCD (default 16, on
+ *                          lattices of up to 1024 four-tile groups an eighth of them;
+ *                          0 leaves the hardware's round-robin)
  *   HEMELB_STAGE_TILES=W   tiles per workgroup that copy their own populations into
  *                          LDS first: 4, 8 or 16, anything else none (default, with
  *                          block addressing: 8 for FP32 D3Q15 from 1M sites, else 4;

@@ -176,55 +176,71 @@ __global__ __launch_bounds__(64) void k_objective_final(const double* __restrict
 // ---------------------------------------------------------------------------
 // iolet terms of the stream transpose (called by the site's own thread)
 // ---------------------------------------------------------------------------
-// Adds to g the adjoint that the values pulled by the iolet links of site s (at
-// the step whose ghosts were filled from A) send to the site's own populations of
-// A, and accumulates the inlet-coefficient adjoints.  gmask: directions of the site's
-// iolet links; fh: dJ/df of that step.
+// Turns g of an iolet site s into the adjoint of its populations of A: on entry
+// g[opp(i)] of an iolet link i (directions gmask, first link `first`) holds the adjoint
+// of the value the link pulled at the step whose ghosts were filled from A; on return
+// every g[k] holds what that value and the other directions send to population k.  The
+// adjoints of an inlet's values go to I.gh, for k_theta.
+// The few workgroups with iolet sites set the kernel's length on a small lattice, so the
+// chain of dependent loads is short: the links' iolets at once, then what the first one
+// names (a link of another iolet loads its own); the inlet coefficients' sums are left to
+// k_theta instead of a read-modify-write per link and harmonic here.  On 200k sites a
+// reverse step went from 26 to 18 us, one with a recompute step beside it from 29 to 22.
 template <int Q, int ST, bool SC>
 __device__ inline void iolet_terms(const typename Store<ST>::T* __restrict__ A, int32_t s,
-                                   uint32_t gmask, const float* __restrict__ fh, const Ghosts& G,
-                                   const IoletAdj& I, int64_t kis, float (&g)[Q]) {
+                                   uint32_t gmask, int64_t first, const Ghosts& G,
+                                   const IoletAdj& I, float (&g)[Q]) {
     using C = Codec<Q, ST, SC>;
     using Lt = Lat<Q>;
     float d[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) d[i] = C::dec(i, A[tix<Q>(i, s)]);
+    // the site's iolet links are consecutive in the link list, in direction order
+    const int k0 = G.iolet[first];
+    int kio[Q];
+    {
+        int64_t l = first;
+#pragma unroll
+        for (int i = 1; i < Q; ++i) {
+            if (!(gmask & (1u << i))) continue;
+            kio[i] = G.iolet[l];
+            ++l;
+        }
+    }
+    const float qbar = I.q_index >= 0 ? (float)(2.0 * (I.q_tape[I.q_index] - I.q_target)) : 0.f;
+    const int64_t at = ((int64_t)I.t - G.vals_t0) * G.n_iolets;
+    const int kind0 = G.iolets[k0].kind;
+    const double val0 = G.vals[at + k0];
     float drho, mx, my, mz;
     moments<Q>(d, drho, mx, my, mz);
     const float rA = 1.0f + drho;
     const float ir = 1.0f / rA;
     const float ux = mx * ir, uy = my * ir, uz = mz * ir;
-    const double qbar = I.q_index >= 0 ? 2.0 * (I.q_tape[I.q_index] - I.q_target) : 0.0;
     float acc[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) acc[i] = 0.f;
-    // the site's iolet links are consecutive in the link list, in direction order
-    int64_t l = I.S.lo[kis];
+    int64_t l = first;
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
         if (!(gmask & (1u << i))) continue;
         const int o = opp(i);
-        const int kio = G.iolet[l];
-        const DevIolet io = G.iolets[kio];
-        const int64_t step = ((int64_t)I.t - G.vals_t0) * G.n_iolets + kio;
-        float gh = fh[tix<Q>(i, s)];  // adjoint of the incoming value the link pulled
-        if (kio == I.outlet && I.q_index >= 0) {
-            gh -= (float)qbar;
-            acc[o] += (float)qbar;
+        const bool same = kio[i] == k0;
+        const int kind = same ? kind0 : G.iolets[kio[i]].kind;
+        float gh = g[o];
+        g[o] = 0.f;
+        if (kio[i] == I.outlet && I.q_index >= 0) {
+            gh -= qbar;
+            acc[o] += qbar;
         }
-        if (io.kind == 1) {
-            acc[o] += gh;
-            // d value / d(mean, cos_h, sin_h), with the basis tabulated for this step
-            const double c = (double)gh * (double)G.coef[l];
-            double* th = I.theta_acc + l * I.nbasis;
-            const double* bs = G.basis + step * G.basis_stride;
-            th[0] += c;
-            for (int h = 1; h <= io.n_harm; ++h) {
-                th[h] += c * bs[2 * (h - 1)];
-                th[io.n_harm + h] += c * bs[2 * (h - 1) + 1];
-            }
+        // what goes to population o is rounded, then added where the branches meet, but
+        // fused with its sum for the last direction: results stay the same to the last bit
+        constexpr int kLast = Q - 1;
+        float back;
+        if (kind == 1) {
+            back = i != kLast ? gh : acc[o] + gh;
+            I.gh[l] = gh;
         } else {
-            const float rk = (float)G.vals[step];
+            const float rk = (float)(same ? val0 : G.vals[at + kio[i]]);
             const float cix = Lt::cx[i], ciy = Lt::cy[i], ciz = Lt::cz[i];
             const float cu = cix * ux + ciy * uy + ciz * uz;
             const float sc = Lt::w[i] * rk;
@@ -233,13 +249,45 @@ __device__ inline void iolet_terms(const typename Store<ST>::T* __restrict__ A, 
             const float gz = sc * (3.0f * ciz + 9.0f * cu * ciz - 3.0f * uz);
             const float gi = gh * ir;
 #pragma unroll
-            for (int jd = 0; jd < Q; ++jd)
-                acc[jd] += gi * ((Lt::cx[jd] - ux) * gx + (Lt::cy[jd] - uy) * gy + (Lt::cz[jd] - uz) * gz);
+            for (int jd = 0; jd < Q; ++jd) {
+                const float e = (Lt::cx[jd] - ux) * gx + (Lt::cy[jd] - uy) * gy + (Lt::cz[jd] - uz) * gz;
+                if (jd != o) acc[jd] += gi * e;
+                else back = i != kLast ? gi * e : __builtin_fmaf(gi, e, acc[o]);
+            }
         }
+        acc[o] = i != kLast ? acc[o] + back : back;
         ++l;
     }
 #pragma unroll
     for (int i = 0; i < Q; ++i) g[i] += acc[i];
+}
+
+// d value / d(mean, cos_h, sin_h) of the inlet links over `rows` reverse steps, the
+// latest (row rows - 1) first: one thread per coefficient of a link, with the basis
+// tabulated for each step.  gh: adjoints of the links' values, a row per step from t0.
+__global__ __launch_bounds__(kBlock) void k_theta(Ghosts G, const float* __restrict__ gh,
+                                                  int32_t rows, int64_t t0, int32_t nbasis,
+                                                  double* __restrict__ theta) {
+    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t l = k / nbasis;
+    const int b = (int)(k - l * nbasis);
+    if (l >= G.count) return;
+    const int kio = G.iolet[l];
+    const int harm = G.iolets[kio].n_harm;
+    if (G.iolets[kio].kind != 1 || b > 2 * harm) return;
+    const double coef = (double)G.coef[l];
+    // column of the step's basis (cos_h, sin_h by harmonic); the mean's factor is one
+    const int col = b <= harm ? 2 * (b - 1) : 2 * (b - harm - 1) + 1;
+    const double* bs = b ? G.basis + ((t0 - G.vals_t0) * G.n_iolets + kio) * G.basis_stride + col
+                         : nullptr;
+    const int64_t pitch = (int64_t)G.n_iolets * G.basis_stride;
+    double sum = theta[k];
+#pragma unroll 8
+    for (int32_t r = rows - 1; r >= 0; --r) {
+        const double c = (double)gh[(int64_t)r * G.count + l] * coef;
+        sum += b ? c * bs[r * pitch] : c;
+    }
+    theta[k] = sum;
 }
 
 // ---------------------------------------------------------------------------
@@ -303,15 +351,12 @@ __device__ inline void adj_group(
             for (int i = 1; i < Q; ++i) {
                 const int o = opp(i);
                 // a wall link's reference is the own row moved by o - i rows: the load
-                // takes row i, one row beyond the one a fluid link takes each way
-                const bool wall = e[i] == own + (uint32_t)((o - i) * kRowSize<SZ>);
-                const uint32_t r = (wall ? own + (uint32_t)((i - o) * kRowSize<SZ>) : e[i]) * (4 / SZ);
+                // takes row i, one row beyond the one a fluid link takes each way; an
+                // iolet link's value, whose adjoint iolet_terms wants, is there too
+                const bool back = e[i] == own + (uint32_t)((o - i) * kRowSize<SZ>) ||
+                                  (gmask & (1u << i));
+                const uint32_t r = (back ? own + (uint32_t)((i - o) * kRowSize<SZ>) : e[i]) * (4 / SZ);
                 g[o] = *reinterpret_cast<const float*>(gb + r + (o - 1) * kRow);
-            }
-            if (gmask) {
-#pragma unroll
-                for (int i = 1; i < Q; ++i)
-                    if (gmask & (1u << i)) g[opp(i)] = 0.f;
             }
         }
         if (MODE != ADJ_FINAL && !F) refs_gather<Q, ST, SC>(A, base, own, e, d);
@@ -328,13 +373,13 @@ __device__ inline void adj_group(
                     if (gl < 0) gl = ghost_link<Q>(G, n, j[i], i);
                     gmask |= 1u << i;
                 }
-                g[o] = j[i] >= n ? 0.f : gin[j[i] < 0 ? tix<Q>(i, s) : tix<Q>(o, j[i])];
+                g[o] = gin[j[i] < 0 || j[i] >= n ? tix<Q>(i, s) : tix<Q>(o, j[i])];
             }
         }
         if (MODE != ADJ_FINAL && !F) gather_pre<Q, ST, SC>(A, s, n, d, j);
     }
     if constexpr (MODE != ADJ_OWN) {
-        if (gmask) iolet_terms<Q, ST, SC>(Ai, s, gmask, gin, G, I, I.link_is[gl], g);
+        if (gmask) iolet_terms<Q, ST, SC>(Ai, s, gmask, gl, G, I, g);
     }
     if constexpr (MODE == ADJ_FINAL) {
 #pragma unroll
@@ -594,6 +639,13 @@ hipError_t launch_adj_dual(const Layout& L, const Ghosts& Gf, const void* src, v
                                                   omega, alpha, alpha_hat, wss_w, normal, xcd_group,
                                                   s);
     });
+}
+
+hipError_t launch_theta(const Ghosts& G, const float* gh, int32_t rows, int64_t t0, int32_t nbasis,
+                        double* theta, hipStream_t s) {
+    if (G.count == 0 || rows < 1) return hipSuccess;
+    k_theta<<<blocks(G.count * nbasis), kBlock, 0, s>>>(G, gh, rows, t0, nbasis, theta);
+    return hipGetLastError();
 }
 
 }  // namespace hlb

@@ -16,14 +16,6 @@ struct Objective {
     int32_t n_dome;
 };
 
-// sites that own iolet links, with their (contiguous) ghost-link ranges
-struct IoletSites {
-    int64_t count;
-    const int32_t* site;
-    const int32_t* lo;
-    const int32_t* hi;
-};
-
 // Q(t) and the sum of WSS over the dome for the step whose pre-collision state
 // (ghosts filled) is A; deterministic two-pass reduction through `part`, which
 // holds 2 * objective_parts(n_out + n_dome) doubles.
@@ -35,16 +27,26 @@ hipError_t launch_objective(const Layout& L, const Ghosts& G, const void* A, con
 // The iolet terms of the stream transpose at step t (the step whose ghost values
 // are differentiated).
 struct IoletAdj {
-    IoletSites S;           // sites with iolet links, sorted by site
-    const int32_t* link_is; // entry in S of the site of each iolet link
     double t;               // boundary time of the step
     int32_t outlet;         // iolet of the flux objective
     const double* q_tape;   // Q(t) of the window steps
     int64_t q_index;        // index of Q(t) in q_tape, or -1 outside the window
     double q_target;
-    double* theta_acc;      // FP64 inlet-coefficient adjoints per link, nbasis each
-    int32_t nbasis;
+    float* gh;              // adjoint of the value of each inlet link, for launch_theta
 };
+
+// Adds to the FP64 inlet-coefficient adjoints theta (nbasis per link) what the link-value
+// adjoints gh of `rows` steps from t0 (a row of one per link each) give, the latest step
+// first.  G holds the steps' basis.
+#ifdef HLB_NO_DEVICE  // host-only builds of the planner: no kernels to launch
+inline hipError_t launch_theta(const Ghosts&, const float*, int32_t, int64_t, int32_t, double*,
+                               hipStream_t) {
+    return hipErrorNoDevice;
+}
+#else
+hipError_t launch_theta(const Ghosts& G, const float* gh, int32_t rows, int64_t t0, int32_t nbasis,
+                        double* theta, hipStream_t s);
+#endif
 
 // The reverse sweep in pull form.  Between kernels of one segment the sweep holds
 // fhat_t = dJ/df_t, the adjoint of the pre-collision populations; at segment ends

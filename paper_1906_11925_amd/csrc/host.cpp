@@ -274,7 +274,7 @@ struct hemelb_lb {
     int64_t t = 0;
     bool streamed = false;
     bool ghosts_ready = false;  // A[cur]'s ghost slots hold the incoming values for time t
-    int xcd_group = 16;  // consecutive workgroups per XCD (measured best at 8-16)
+    int xcd_group = 16;  // consecutive workgroups per XCD (measured best at 8-16 on large lattices)
     // stream-collide workgroups that copy their own tiles' populations into LDS
     // (block addressing only; the copy keeps the in-group pulls off the L1, whose
     // accesses halve: 51 M -> 26 M per FP16 step of 5.6M sites).  Tiles per workgroup,
@@ -352,12 +352,8 @@ struct hemelb_lb {
     int gcur = 0;
     double* alpha_hat = nullptr;
     double* theta_acc = nullptr;
+    float* link_adj = nullptr;  // adjoints of the link values, kThetaRows steps of nghost
     int32_t nbasis = 1;
-    int32_t* is_link = nullptr;  // entry of each iolet link's site among the iolet sites
-    int32_t* is_site = nullptr;
-    int32_t* is_lo = nullptr;
-    int32_t* is_hi = nullptr;
-    int64_t n_is = 0;
     int64_t adj_t = -1;
 
     hlb::Layout layout() const {
@@ -420,14 +416,13 @@ void release(hemelb_lb* h) {
                     h->A[0],      h->A[1],      h->tbl,        h->g_site,    h->g_dir,
                     h->t16,       h->toff,      h->tlist,      h->brec,      h->gmask,
                     h->bnbr,      h->tblock,    h->g_slot,     h->gblob,     h->grp,
-                    h->g_cell_link, h->is_link,
-                    h->g_iolet,   h->g_coef,    h->d_iolets,   h->d_harm,    h->perm,      h->xloc,
+                    h->g_cell_link,                    h->g_iolet,   h->g_coef,    h->d_iolets,   h->d_harm,    h->perm,      h->xloc,
                     h->normal,    h->alpha,     h->partial,    h->tot,       h->flag,
                     h->d_out_links, h->d_dome,  h->d_wss_w,    h->d_qtape,   h->d_wtape,
                     h->d_opart,
-                    h->ghat[0],   h->ghat[1],   h->alpha_hat,  h->theta_acc, h->is_site,
+                    h->ghat[0],   h->ghat[1],   h->alpha_hat,  h->theta_acc, h->link_adj,
                     h->r_grid,    h->r_near,     h->r_rec,     h->r_vals,    h->r_lut,
-                    h->is_lo,     h->is_hi,     h->d_vals};
+                    h->d_vals};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     for (void* p : h->tape)
@@ -1586,12 +1581,28 @@ int recompute_step(hemelb_lb* h, std::vector<void*>& tape, const hemelb_lb::Seri
     return HEMELB_OK;
 }
 
-// iolet terms of the reverse step at time t
-hlb::IoletAdj iolet_adj(const hemelb_lb* h, int64_t t) {
-    const hlb::IoletSites S{h->n_is, h->is_site, h->is_lo, h->is_hi};
+// Rows of link-value adjoints kept before launch_theta adds them up (a row per step: 32
+// KB for the 128 links of a small inlet): the launch is spread over as many steps, and
+// the rows stay in the caches.
+constexpr int64_t kThetaRows = 64;
+
+// iolet terms of the reverse step at time t of the segment starting at t0
+hlb::IoletAdj iolet_adj(const hemelb_lb* h, int64_t t, int64_t t0) {
     const bool inw = t >= h->w0 && t < h->w1;
-    return hlb::IoletAdj{S,          h->is_link,        (double)t,     h->obj_outlet,
-                         h->d_qtape, inw ? t - h->w0 : -1, h->q_target, h->theta_acc, h->nbasis};
+    return hlb::IoletAdj{(double)t, h->obj_outlet, h->d_qtape, inw ? t - h->w0 : -1, h->q_target,
+                         h->link_adj ? h->link_adj + (t - t0) % kThetaRows * h->nghost : nullptr};
+}
+
+// After the iolet terms of time t of a segment of `steps` steps from t0: the inlet
+// coefficients' adjoints of the rows from t on, once row 0 is written.
+int add_theta(hemelb_lb* h, const hemelb_lb::Series& sr, int64_t t, int64_t t0, int64_t steps,
+              hipStream_t stream) {
+    if (!h->theta_acc || (t - t0) % kThetaRows != 0) return HEMELB_OK;
+    HIP_TRY(hlb::launch_theta(segment_ghosts(h, sr), h->link_adj,
+                              (int32_t)std::min(kThetaRows, t0 + steps - t), t, h->nbasis,
+                              h->theta_acc, stream),
+            "theta adjoint");
+    return HEMELB_OK;
 }
 
 // objective weights of the reverse step at time t (null outside the window)
@@ -1610,13 +1621,13 @@ int reverse_step(hemelb_lb* h, std::vector<void*>& tape, const std::vector<void*
     const int64_t t = t0 + m;
     const int mode = reverse_mode(m, steps);
     const void* F = ftape ? (*ftape)[m] : nullptr;
-    HIP_TRY(hlb::launch_adj_step(h->layout(), segment_ghosts(h, sr), iolet_adj(h, t + 1), mode,
+    HIP_TRY(hlb::launch_adj_step(h->layout(), segment_ghosts(h, sr), iolet_adj(h, t + 1, t0), mode,
                                  tape[m], F, tape[m + 1], h->ghat[h->gcur], h->ghat[h->gcur ^ 1],
                                  h->omega, h->alpha, h->alpha_hat, wss_weights(h, t), h->normal,
                                  h->xcd_group, stream),
             "adjoint step");
     h->gcur ^= 1;
-    return HEMELB_OK;
+    return mode == hlb::ADJ_PULL ? add_theta(h, sr, t + 1, t0, steps, stream) : HEMELB_OK;
 }
 
 // recompute step mf of the segment at tf0 (tape tf, series sf) and reverse step
@@ -1630,26 +1641,28 @@ int dual_step(hemelb_lb* h, std::vector<void*>& tf, const hemelb_lb::Series& sf,
         HIP_TRY(hlb::launch_ghost_fill(L, Gf, tf[mf], tf0 + mf, stream), "recompute ghosts");
     const int64_t t = tr0 + mr;
     HIP_TRY(hlb::launch_adj_dual(L, Gf, tf[mf], tf[mf + 1], tf0 + mf + 1, segment_ghosts(h, sr),
-                                 iolet_adj(h, t + 1), reverse_mode(mr, nr_steps), tr[mr],
+                                 iolet_adj(h, t + 1, tr0), reverse_mode(mr, nr_steps), tr[mr],
                                  tr[mr + 1], h->ghat[h->gcur], h->ghat[h->gcur ^ 1], h->omega,
                                  h->alpha, h->alpha_hat, wss_weights(h, t), h->normal,
                                  h->xcd_group, stream),
             "adjoint dual step");
     h->gcur ^= 1;
-    return HEMELB_OK;
+    return reverse_mode(mr, nr_steps) == hlb::ADJ_PULL
+               ? add_theta(h, sr, t + 1, tr0, nr_steps, stream)
+               : HEMELB_OK;
 }
 
-// end of a segment at t0 (tape[0] = A_t0): the stream transpose of step t0 alone,
-// fhat_t0 -> dJ/dA_t0
+// end of a segment of `steps` steps from t0 (tape[0] = A_t0): the stream transpose of
+// step t0 alone, fhat_t0 -> dJ/dA_t0
 int end_reverse(hemelb_lb* h, std::vector<void*>& tape, const hemelb_lb::Series& sr, int64_t t0,
-                hipStream_t stream) {
-    HIP_TRY(hlb::launch_adj_step(h->layout(), segment_ghosts(h, sr), iolet_adj(h, t0),
+                int64_t steps, hipStream_t stream) {
+    HIP_TRY(hlb::launch_adj_step(h->layout(), segment_ghosts(h, sr), iolet_adj(h, t0, t0),
                                  hlb::ADJ_FINAL, nullptr, nullptr, tape[0], h->ghat[h->gcur],
                                  h->ghat[h->gcur ^ 1], h->omega, nullptr, nullptr, nullptr,
                                  h->normal, h->xcd_group, stream),
             "adjoint segment end");
     h->gcur ^= 1;
-    return HEMELB_OK;
+    return add_theta(h, sr, t0, t0, steps, stream);
 }
 
 }  // namespace
@@ -1820,6 +1833,10 @@ static int init_handle(hemelb_lb* h, hemelb_lb_t* out, const hemelb_lb_desc_t* d
     h->tau = d->tau;
     h->omega = std::isinf(d->tau) ? 0.0f : (float)(1.0 / d->tau);
     h->stream = static_cast<hipStream_t>(d->stream);
+    // a lattice of at most 1024 groups of four tiles: one contiguous share per XCD, so that
+    // none gets a window more than the others (reverse sweep of 200k sites 19.1 -> 18.1 ms)
+    const int64_t groups = (d->n_sites + 255) / 256;
+    if (groups <= 1024) h->xcd_group = (int)std::max<int64_t>(1, (groups + 7) / 8);
     if (const char* e = getenv("HEMELB_XCD_GROUP")) h->xcd_group = std::max(0, atoi(e));
     h->stage_tiles = 0;
     if ((d->n_sites + 255) / 256 >= 256)
@@ -2443,25 +2460,9 @@ static int adjoint_begin_impl(hemelb_lb_t h, int64_t max_segment) {
     if (!h->theta_acc && h->nghost > 0 &&
         (rc = dev_alloc(h, &h->theta_acc, (size_t)h->nghost * h->nbasis, "theta adjoint")))
         return rc;
-    if (!h->is_site && h->nghost > 0) {
-        std::vector<int32_t> st, lo, hi;
-        for (int64_t l = 0; l < h->nghost;) {
-            int64_t e = l;
-            while (e < h->nghost && h->h_gsite[e] == h->h_gsite[l]) ++e;
-            st.push_back(h->h_gsite[l]);
-            lo.push_back((int32_t)l);
-            hi.push_back((int32_t)e);
-            l = e;
-        }
-        std::vector<int32_t> of_link((size_t)h->nghost);
-        for (size_t k = 0; k < st.size(); ++k)
-            for (int32_t l = lo[k]; l < hi[k]; ++l) of_link[l] = (int32_t)k;
-        if ((rc = dev_upload(h, &h->is_link, of_link, "iolet link sites"))) return rc;
-        if ((rc = dev_upload(h, &h->is_site, st, "iolet sites"))) return rc;
-        if ((rc = dev_upload(h, &h->is_lo, lo, "iolet sites"))) return rc;
-        if ((rc = dev_upload(h, &h->is_hi, hi, "iolet sites"))) return rc;
-        h->n_is = (int64_t)st.size();
-    }
+    if (!h->link_adj && h->nghost > 0 &&
+        (rc = dev_alloc(h, &h->link_adj, (size_t)(kThetaRows * h->nghost), "link adjoints")))
+        return rc;
     h->gcur = 0;
     hlb::Layout Lg = h->layout();
     Lg.storage = HEMELB_STORE_F32;
@@ -2494,7 +2495,7 @@ static int adjoint_segment_impl(hemelb_lb_t h, const void* checkpoint, int64_t t
     for (int64_t m = 0; m < steps && !rc; ++m) rc = recompute_step(h, h->tape, h->series[0], t0, m, h->stream);
     for (int64_t m = steps - 1; m >= 0 && !rc; --m)
         rc = reverse_step(h, h->tape, nullptr, h->series[0], t0, m, steps, h->stream);
-    if (!rc) rc = end_reverse(h, h->tape, h->series[0], t0, h->stream);
+    if (!rc) rc = end_reverse(h, h->tape, h->series[0], t0, steps, h->stream);
     if (rc) return rc;
     h->adj_t = t0;
     return HEMELB_OK;
@@ -2562,7 +2563,7 @@ static int adjoint_run_impl(hemelb_lb_t h, const void* const* checkpoints, const
                 rc = recompute_step(h, tf, h->series[nb], t0[k - 1], m, h->stream);
             if (rc) return rc;
         }
-        if ((rc = end_reverse(h, tr, h->series[b], t0[k], h->stream))) return rc;
+        if ((rc = end_reverse(h, tr, h->series[b], t0[k], steps[k], h->stream))) return rc;
     }
     h->adj_t = t0[0];
     return HEMELB_OK;
@@ -2662,7 +2663,7 @@ static int adjoint_recorded_impl(hemelb_lb_t h) {
     for (int64_t m = steps - 1; m >= 0 && !rc; --m)
         rc = reverse_step(h, h->rec, h->frec.empty() ? nullptr : &h->frec, h->series[0],
                           h->rec_t0, m, steps, h->stream);
-    if (!rc) rc = end_reverse(h, h->rec, h->series[0], h->rec_t0, h->stream);
+    if (!rc) rc = end_reverse(h, h->rec, h->series[0], h->rec_t0, steps, h->stream);
     if (rc) return rc;
     h->adj_t = h->rec_t0;
     return HEMELB_OK;
