@@ -14,10 +14,25 @@ struct Objective {
     int32_t n_out;
     const int32_t* dome;       // Morton indices of dome sites with a wall normal
     int32_t n_dome;
+    // laid out once per objective by launch_objective_tables
+    int64_t* out_at;       // [2][n_out] where a link's outgoing and incoming population lie
+    int32_t* dome_link;    // [q - 1][n_dome] links of the dome sites
+    float* dome_normal;    // [3][n_dome] their wall normals
+    uint32_t* ticket;      // blocks of a launch that are done; zero between launches
 };
 
+#ifdef HLB_NO_DEVICE  // host-only builds of the planner: no kernels to launch
+inline hipError_t launch_objective_tables(const Layout&, const Ghosts&, const Objective&,
+                                          const float*, hipStream_t) {
+    return hipErrorNoDevice;
+}
+#else
+hipError_t launch_objective_tables(const Layout& L, const Ghosts& G, const Objective& O,
+                                   const float* normal, hipStream_t s);
+#endif
+
 // Q(t) and the sum of WSS over the dome for the step whose pre-collision state
-// (ghosts filled) is A; deterministic two-pass reduction through `part`, which
+// (ghosts filled) is A; deterministic reduction through `part`, which
 // holds 2 * objective_parts(n_out + n_dome) doubles.
 int32_t objective_parts(int64_t items);
 hipError_t launch_objective(const Layout& L, const Ghosts& G, const void* A, const Objective& O,

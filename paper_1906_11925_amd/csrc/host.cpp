@@ -330,6 +330,10 @@ struct hemelb_lb {
     double* d_qtape = nullptr;
     double* d_wtape = nullptr;
     double* d_opart = nullptr;  // partial sums of the objective's blocks
+    int64_t* d_out_at = nullptr;  // the objective's tables (hlb::Objective)
+    int32_t* d_dome_link = nullptr;
+    float* d_dome_normal = nullptr;
+    uint32_t* d_ticket = nullptr;
     int64_t obj_bytes = 0;      // device bytes of the objective's arrays
 
     // adjoint
@@ -367,6 +371,10 @@ struct hemelb_lb {
         return hlb::Ghosts{nghost,  g_slot,   g_cell_link, g_site,  g_dir,   g_iolet,
                            g_coef,  d_iolets, d_harm,      d_vals,  vals_t0, n_iolets,
                            nullptr, basis_stride};
+    }
+    hlb::Objective objective() const {
+        return hlb::Objective{d_out_links, n_out,         d_dome,  (int32_t)n_dome, d_out_at,
+                              d_dome_link, d_dome_normal, d_ticket};
     }
     size_t elem() const { return storage == HEMELB_STORE_F32 ? 4 : 2; }
     // algorithmic HBM bytes of one site update: populations read and written once,
@@ -416,10 +424,11 @@ void release(hemelb_lb* h) {
                     h->A[0],      h->A[1],      h->tbl,        h->g_site,    h->g_dir,
                     h->t16,       h->toff,      h->tlist,      h->brec,      h->gmask,
                     h->bnbr,      h->tblock,    h->g_slot,     h->gblob,     h->grp,
-                    h->g_cell_link,                    h->g_iolet,   h->g_coef,    h->d_iolets,   h->d_harm,    h->perm,      h->xloc,
+                    h->g_cell_link,
+                    h->g_iolet,   h->g_coef,    h->d_iolets,   h->d_harm,    h->perm,      h->xloc,
                     h->normal,    h->alpha,     h->partial,    h->tot,       h->flag,
                     h->d_out_links, h->d_dome,  h->d_wss_w,    h->d_qtape,   h->d_wtape,
-                    h->d_opart,
+                    h->d_opart,   h->d_out_at,  h->d_dome_link, h->d_dome_normal, h->d_ticket,
                     h->ghat[0],   h->ghat[1],   h->alpha_hat,  h->theta_acc, h->link_adj,
                     h->r_grid,    h->r_near,     h->r_rec,     h->r_vals,    h->r_lut,
                     h->d_vals};
@@ -887,7 +896,7 @@ int do_step(hemelb_lb* h) {
     if (!h->ghosts_ready)
         HIP_TRY(hlb::launch_ghost_fill(L, h->ghosts(), src, h->t, h->stream), "ghost fill");
     if (h->obj_set && h->t >= h->w0 && h->t < h->w1) {
-        const hlb::Objective O{h->d_out_links, h->n_out, h->d_dome, (int32_t)h->n_dome};
+        const hlb::Objective O = h->objective();
         HIP_TRY(hlb::launch_objective(L, h->ghosts(), src, O, h->normal, h->omega, h->d_opart,
                                       h->d_qtape + (h->t - h->w0), h->d_wtape + (h->t - h->w0),
                                       h->stream),
@@ -2338,7 +2347,8 @@ static int set_objective_impl(hemelb_lb_t h, const hemelb_objective_t* obj) {
     if (!h) return fail(HEMELB_EINVAL, "NULL handle");
     HIP_TRY(hipStreamSynchronize(h->stream), "sync");
     for (void** p : {(void**)&h->d_out_links, (void**)&h->d_dome, (void**)&h->d_wss_w,
-                     (void**)&h->d_qtape, (void**)&h->d_wtape, (void**)&h->d_opart})
+                     (void**)&h->d_qtape, (void**)&h->d_wtape, (void**)&h->d_opart, (void**)&h->d_out_at, (void**)&h->d_dome_link,
+                     (void**)&h->d_dome_normal, (void**)&h->d_ticket})
         if (*p) {
             (void)hipFree(*p);
             *p = nullptr;
@@ -2379,9 +2389,16 @@ static int set_objective_impl(hemelb_lb_t h, const hemelb_objective_t* obj) {
     if ((rc = dev_upload(h, &h->d_opart, parts, "objective partials"))) return rc;
     if ((rc = dev_upload(h, &h->d_qtape, zeros, "flux tape"))) return rc;
     if ((rc = dev_upload(h, &h->d_wtape, zeros, "shear tape"))) return rc;
+    if ((rc = dev_alloc(h, &h->d_out_at, 2 * outl.size(), "objective tables"))) return rc;
+    if ((rc = dev_alloc(h, &h->d_dome_link, (h->q - 1) * dome.size(), "objective tables"))) return rc;
+    if ((rc = dev_alloc(h, &h->d_dome_normal, 3 * dome.size(), "objective tables"))) return rc;
+    if ((rc = dev_upload(h, &h->d_ticket, std::vector<uint32_t>{0}, "objective tables"))) return rc;
     h->obj_bytes = h->device_bytes - before;
     h->n_out = (int32_t)outl.size();
     h->n_dome = (int64_t)dome.size();
+    HIP_TRY(hlb::launch_objective_tables(h->layout(), h->ghosts(), h->objective(), h->normal,
+                                         h->stream),
+            "objective tables");
     h->obj_outlet = obj->outlet;
     h->q_target = obj->q_target;
     h->lam = obj->lam;
