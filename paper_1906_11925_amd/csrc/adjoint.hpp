@@ -50,6 +50,16 @@ struct IoletAdj {
     float* gh;              // adjoint of the value of each inlet link, for launch_theta
 };
 
+// out[perm[m]] = a[m] for the n sites (null perm: identity).
+#ifdef HLB_NO_DEVICE  // host-only builds of the planner: no kernels to launch
+inline hipError_t launch_order_alpha(const double*, const int32_t*, int64_t, double*, hipStream_t) {
+    return hipErrorNoDevice;
+}
+#else
+hipError_t launch_order_alpha(const double* a, const int32_t* perm, int64_t n, double* out,
+                              hipStream_t s);
+#endif
+
 // Adds to the FP64 inlet-coefficient adjoints theta (nbasis per link) what the link-value
 // adjoints gh of `rows` steps from t0 (a row of one per link each) give, the latest step
 // first.  G holds the steps' basis.

@@ -2696,11 +2696,17 @@ static int adjoint_grads_impl(hemelb_lb_t h, double* dtheta, double* dalpha) {
     if (h->adj_t < 0) return fail(HEMELB_EORDER, "no adjoint run");
     HIP_TRY(hipStreamSynchronize(h->stream), "sync");
     if (dalpha) {
-        std::vector<double> a(h->n, 0.0);
-        if (h->n > 0)
-            HIP_TRY(hipMemcpy(a.data(), h->alpha_hat, h->n * sizeof(double), hipMemcpyDeviceToHost),
+        // the buffer the next reverse step writes (q FP32 values a site) is free between calls
+        double* ordered = reinterpret_cast<double*>(h->ghat[h->gcur ^ 1]);
+        if (h->n > 0) {
+            HIP_TRY(hipSetDevice(h->device), "set device");
+            HIP_TRY(hlb::launch_order_alpha(h->alpha_hat, h->perm, h->n, ordered, h->stream),
                     "alpha adjoint");
-        for (int64_t m = 0; m < h->n; ++m) dalpha[h->order[m]] = a[m];
+            HIP_TRY(hipMemcpyAsync(dalpha, ordered, h->n * sizeof(double), hipMemcpyDeviceToHost,
+                                   h->stream),
+                    "alpha adjoint");
+            HIP_TRY(hipStreamSynchronize(h->stream), "sync");
+        }
     }
     if (dtheta) {
         std::vector<double> acc((size_t)h->nghost * h->nbasis, 0.0);
