@@ -300,6 +300,7 @@ struct hemelb_lb {
     std::vector<int32_t> h_coords;  // [n][3] site coordinates in Morton order (when given)
     int32_t* r_grid = nullptr;
     uint8_t* r_near = nullptr;
+    uint8_t* r_far = nullptr;
     hlb::BlockRec* r_rec = nullptr;
     float* r_vals = nullptr;
     float* r_lut = nullptr;
@@ -430,7 +431,7 @@ void release(hemelb_lb* h) {
                     h->d_out_links, h->d_dome,  h->d_wss_w,    h->d_qtape,   h->d_wtape,
                     h->d_opart,   h->d_out_at,  h->d_dome_link, h->d_dome_normal, h->d_ticket,
                     h->ghat[0],   h->ghat[1],   h->alpha_hat,  h->theta_acc, h->link_adj,
-                    h->r_grid,    h->r_near,     h->r_rec,     h->r_vals,    h->r_lut,
+                    h->r_grid,    h->r_near,     h->r_far,     h->r_rec,     h->r_vals,    h->r_lut,
                     h->d_vals};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -1466,6 +1467,33 @@ int64_t planned_device_bytes(const HostPlan& P, int q, size_t elem) {
     return b;
 }
 
+// distance maps of the renderer: to a block in trilinear reach (flags `near`, one more cell
+// per axis than the block map) and to a block with a site
+int render_distances(hemelb_lb_t h, const std::vector<uint8_t>& near) {
+    const int32_t ext[3] = {h->r_gdim[0] + 1, h->r_gdim[1] + 1, h->r_gdim[2] + 1};
+    const size_t cells = (size_t)h->r_gdim[0] * h->r_gdim[1] * h->r_gdim[2];
+    uint8_t *flags = nullptr, *tmp = nullptr;
+    int rc = dev_upload(h, &flags, near, "render reach map");
+    if (!rc) rc = dev_alloc(h, &tmp, near.size(), "render reach map");
+    if (!rc) rc = dev_alloc(h, &h->r_near, near.size(), "render reach map");
+    if (!rc) rc = dev_alloc(h, &h->r_far, cells, "render distance map");
+    hipError_t e = hipSuccess;
+    if (!rc) {
+        e = hlb::launch_render_far(nullptr, flags, ext, tmp, h->r_near, h->stream);
+        if (e == hipSuccess)
+            e = hlb::launch_render_far(h->r_grid, nullptr, h->r_gdim, tmp, h->r_far, h->stream);
+        const hipError_t done = hipStreamSynchronize(h->stream);  // before the flags are freed
+        if (e == hipSuccess) e = done;
+    }
+    for (uint8_t* p : {flags, tmp})
+        if (p) {
+            (void)hipFree(p);
+            h->device_bytes -= (int64_t)near.size();
+        }
+    if (!rc && e != hipSuccess) return hip_fail(e, "render distance map");
+    return rc;
+}
+
 // block map of the sites for the renderer
 int build_render_volume(hemelb_lb_t h) {
     const int64_t n = h->n;
@@ -1520,7 +1548,7 @@ int build_render_volume(hemelb_lb_t h) {
     }
     int rc;
     if ((rc = dev_upload(h, &h->r_grid, grid, "render block map"))) return rc;
-    if ((rc = dev_upload(h, &h->r_near, near, "render reach map"))) return rc;
+    if ((rc = render_distances(h, near))) return rc;
     if ((rc = dev_upload(h, &h->r_rec, rec, "render block records"))) return rc;
     if ((rc = dev_alloc(h, &h->r_vals, (size_t)std::max<int64_t>(n, 1), "render values"))) return rc;
     if ((rc = dev_alloc(h, &h->r_lut, 256 * 4, "render table"))) return rc;
@@ -2244,6 +2272,7 @@ static int render_impl(hemelb_lb_t h, const float* values, const hemelb_view_t* 
                         h->r_rec,
                         h->r_vals,
                         h->r_near,
+                        h->r_far,
                         {h->r_blo[0], h->r_blo[1], h->r_blo[2]},
                         {h->r_gdim[0], h->r_gdim[1], h->r_gdim[2]}};
     hlb::RenderView v{};
