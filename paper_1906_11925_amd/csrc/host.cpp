@@ -787,10 +787,6 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
             ghosts = true;
             fits = fits && inside(n) && inside(n + P.rec[b].goff + hlb::kTile - 1);
         }
-        if (!fits) {
-            P.fallback_bytes += global_bytes;
-            continue;
-        }
         const size_t row_words = (size_t)nown * hlb::kRowBytes / 4;
         const size_t at = P.blob.size();
         P.blob.resize(at + row_words + recs.size() * 4, 0);
@@ -804,7 +800,8 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
             }
             std::memcpy(&P.blob[at + row_words + 4 * r], &c, sizeof c);
         }
-        P.grp[2 * g + 1] = nown | (int32_t)(recs.size() << 16) | (ghosts ? hlb::kGroupGhosts : 0);
+        P.grp[2 * g + 1] = nown | (int32_t)(recs.size() << 16) | (ghosts ? hlb::kGroupGhosts : 0) |
+                           (fits ? 0 : hlb::kGroupFar);
     }
     if (P.blob.empty()) P.blob.assign(4, 0);
 

@@ -83,13 +83,14 @@ constexpr int kRowBytes = 64;
 constexpr int kStageRows = 24;
 constexpr int kStageRecs = 160;
 constexpr int32_t kGroupGhosts = 0x8000;
+constexpr int32_t kGroupFar = 0x4000;  // sources outside the window of group_base
 constexpr int kStageChunks = kStageRows * kRowBytes / 16 + kStageRecs;  // <= threads per workgroup
 
 // Sources of a staged group's links are 32-bit references: the element offset of the
 // source's first population row (tile * q * 64 + lane) from the group's base, plus one
 // row.  The base is the start of the buffer, or, for a lattice whose FP32 buffer
-// reaches past 4 GiB, 2^29 elements below the group's first tile (the host leaves a
-// group whose sources lie outside that window to the global records).
+// reaches past 4 GiB, 2^29 elements below the group's first tile (the host marks a
+// group whose sources lie outside that window).
 constexpr int64_t kRefBack = (int64_t)1 << 29;
 constexpr int64_t kRefSpan = ((int64_t)1 << 30) - 4096;  // references stay below 2^30
 inline __host__ __device__ int64_t group_base(bool wide, int32_t tile, int q) {

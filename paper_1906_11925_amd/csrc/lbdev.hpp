@@ -280,6 +280,10 @@ struct StageHdr {
     int32_t off;
     int nown, nrec;
     bool ghosts;
+    // own blocks of a group with records but sources too far apart for references (nown
+    // is 0 then): the step decodes its links to slots (staged_slots), other kernels take
+    // the global records
+    int far = 0;
 };
 
 // The group entries never change during a launch: read them through the constant
@@ -290,7 +294,9 @@ __device__ inline StageHdr stage_header(const Table& tb, int32_t g) {
     const __attribute__((address_space(4))) int32_t* grp =
         (const __attribute__((address_space(4))) int32_t*)tb.grp;
     const int32_t cnt = grp[2 * g + 1];
-    return StageHdr{grp[2 * g], cnt & 0xff, cnt >> 16, (cnt & kGroupGhosts) != 0};
+    const bool far = (cnt & kGroupFar) != 0;
+    return StageHdr{grp[2 * g], far ? 0 : cnt & 0xff, cnt >> 16, (cnt & kGroupGhosts) != 0,
+                    far ? cnt & 0xff : 0};
 }
 
 // bytes of one population row of a tile
@@ -399,6 +405,28 @@ __device__ inline void staged_refs(const Table& tb, const StageHdr& h, int t, ui
             e[i] = slot_ref<Q, SZ>(tb.n + tb.brec[b].goff + __popcll(gm) - 1, base);
             gmask |= 1u << i;
         }
+    }
+}
+
+// As staged_refs, but the links themselves (sites, walls, ghost slots), for groups whose
+// sources lie too far apart for 32-bit references.  8% of the groups of a 395M-site tree
+// are such: with the global records for them its step took 11.15 ms, so 9.25.
+template <int Q>
+__device__ inline void staged_slots(const Table& tb, const StageHdr& h, int t, const StageLds& lds,
+                                    const LinkLds<Q>& links, int32_t (&j)[Q]) {
+    const char* raw = reinterpret_cast<const char*>(lds.chunk);
+    const uint32_t at = lds.at[t];
+    const uint32_t* lk = reinterpret_cast<const uint32_t*>(&links.q[0][at & 63u]);
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        const uint32_t l = lk[(i - 1) / 4 * (kTile * 4) + (i - 1) % 4];
+        const uint32_t a = *reinterpret_cast<const uint16_t*>(raw + (at & ~63u) + (l >> 16));
+        const uint4 r = *reinterpret_cast<const uint4*>(raw + a);
+        const uint64_t m = (((uint64_t)r.y << 32) | r.x) << (l & 63u);
+        j[i] = (int64_t)m < 0 ? (int32_t)r.z + __popcll(m) : (int32_t)0x80000000u;
+        if (!h.ghosts || (int64_t)m < 0 || (int32_t)r.w < 0) continue;
+        const uint64_t gm = tb.gmask[r.w] << (l & 63u);
+        if ((int64_t)gm < 0) j[i] = tb.n + tb.brec[r.w].goff + __popcll(gm) - 1;
     }
 }
 

@@ -311,7 +311,9 @@ __device__ inline void stream_collide_staged(const typename Store<ST>::T* __rest
     StageLds& map = lds[wave >> 2];
     StageHdr h{0, 0, 0, false};
     if (((int64_t)g << 8) < n) h = stage_header(tb, g);
-    if (h.nown > 0) stage(tb, h, g, t, map);
+    StageHdr hs = h;
+    if (h.far) hs.nown = h.far;
+    if (hs.nown > 0) stage(tb, hs, g, t, map);
     const int64_t base = group_base(tb.wide, 4 * g, Q);
     lds_loads_done();
     __syncthreads();
@@ -319,8 +321,13 @@ __device__ inline void stream_collide_staged(const typename Store<ST>::T* __rest
     if ((s & ~(kTile - 1)) >= n) return;
     if (h.nown == 0) {
         int32_t j[Q];
-        links_blocks_wave<Q>(tb, s, j);
-        if (s >= n) return;
+        if (h.far) {
+            if (s >= n) return;
+            staged_slots<Q>(tb, hs, t, map, links, j);
+        } else {
+            links_blocks_wave<Q>(tb, s, j);
+            if (s >= n) return;
+        }
         site_update<Q, ST, SC, BRINK, false, FOUT>(src, dst, n, omega, alpha, G, t_next, s, j, fout);
         return;
     }
