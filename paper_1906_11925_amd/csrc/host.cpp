@@ -2425,6 +2425,8 @@ static int set_objective_impl(hemelb_lb_t h, const hemelb_objective_t* obj) {
     HIP_TRY(hlb::launch_objective_tables(h->layout(), h->ghosts(), h->objective(), h->normal,
                                          h->stream),
             "objective tables");
+    // the next step may be asked for on another stream
+    HIP_TRY(hipStreamSynchronize(h->stream), "objective tables");
     h->obj_outlet = obj->outlet;
     h->q_target = obj->q_target;
     h->lam = obj->lam;

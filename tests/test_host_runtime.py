@@ -1,0 +1,87 @@
+"""What the host library asks of the HIP runtime, on the CPU.
+
+The built library runs in a child process against a stand-in for the runtime
+(tests/native/hip_stand_in.cpp) that logs launches, allocations and waits instead of doing
+them and can refuse a call.  So the order of launches and waits, the launches of a step
+request and the answers to a full device are checked without a GPU.
+"""
+
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, os, sys
+import numpy as np
+sys.modules["torch"] = None  # the library must bind to the stand-in, not to torch's runtime
+hip = ctypes.CDLL({stand_in!r}, mode=ctypes.RTLD_GLOBAL)
+hip.stand_in_log.restype = ctypes.c_char_p
+hip.stand_in_live.restype = ctypes.c_int64
+hip.stand_in_limit.argtypes = [ctypes.c_int64]
+THEN = ctypes.CFUNCTYPE(None)
+hip.stand_in_at_launch.argtypes = [ctypes.c_char_p, ctypes.c_int, THEN]
+import workloads as wl
+from paper_1906_11925_amd import lib as L
+from paper_1906_11925_amd.lb import _desc, links
+lib = L.load(build_if_missing=False)
+
+def create(nbr, tau, stream=None, **kw):
+    d, keep = _desc(nbr, tau, stream_ptr=stream, **kw)
+    h = ctypes.c_void_p()
+    L.check(lib.hemelb_lb_create(ctypes.byref(h), ctypes.byref(d)))
+    return h
+
+def vessel(g, stream=None, lattice=15, **kw):
+    coords, nbr = links(g.labels, g.shape, g.periodic, lattice)
+    return create(nbr, g.tau, stream, lattice=lattice, coords=coords, iolets=list(g.iolets),
+                  site_weight=g.site_weight(), **kw)
+
+def events():
+    return hip.stand_in_log().decode().splitlines()
+
+def launches(name):
+    return [k for k, e in enumerate(events()) if e.startswith("launch") and name in e]
+
+def info(h):
+    i = L.InfoT()
+    L.check(lib.hemelb_lb_info(h, ctypes.byref(i)))
+    return i
+"""
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory, lib):
+    out = str(tmp_path_factory.mktemp("hip") / "libhip_stand_in.so")
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-std=c++17", "-Wall", "-o", out,
+                    os.path.join(ROOT, "tests", "native", "hip_stand_in.cpp")], check=True)
+    return out
+
+
+def _run(stand_in, code, **env):
+    e = {k: v for k, v in os.environ.items() if not k.startswith("HEMELB_")}
+    e.update(env)
+    res = subprocess.run([sys.executable, "-c", PRELUDE.format(stand_in=stand_in) + textwrap.dedent(code)],
+                         cwd=ROOT, env=e, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-4000:]
+    return res.stdout
+
+
+def test_set_objective_returns_with_its_tables_laid_out(stand_in):
+    """Later work may go to another stream, so nothing of the call may still be queued."""
+    _run(stand_in, """
+        g = wl.pipe()
+        h = vessel(g, stream=0x10)
+        hip.stand_in_clear()
+        dome = np.ones(g.n_sites, dtype=np.uint8)
+        o = L.ObjectiveT(outlet=1, q_target=0.1, dome=dome.ctypes.data_as(L.P(ctypes.c_uint8)),
+                         lam=1.0, t0=0, t1=4)
+        L.check(lib.hemelb_lb_set_objective(h, ctypes.byref(o)))
+        last = launches("k_objective_tables")[-1]
+        assert events()[last].endswith(" 16")
+        assert "sync 16" in events()[last + 1:], events()
+    """)
