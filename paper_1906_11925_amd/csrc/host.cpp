@@ -1050,8 +1050,12 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
                 count[k] = (int32_t)site.size();
             }
             for (int32_t m : site) seen[m] = 0;
-            // the steps between the first and the last hold one site per thread
-            return count[steps - 1] <= pitch && (steps == 2 || count[steps - 2] <= threads);
+            // a row's codes count to the last local number in 16 bits; the steps between the
+            // first and the last hold one site per thread
+            const int64_t all = count[steps];
+            return count[steps - 1] <= pitch &&
+                   (pitch + all + (all > pitch ? pitch : 0)) * elem <= 1 << 16 &&
+                   (steps == 2 || count[steps - 2] <= threads);
         };
         const int64_t end = ttiles * (w + 1) / nt;
         for (int64_t T = ttiles * w / nt; T < end && p.fits;) {
