@@ -221,8 +221,9 @@ static hipError_t fuse_dispatch(const Layout& L, bool brink, int pitch, F&& f) {
 
 hipError_t fuse_prepare(const Layout& L, const Fuse& F, bool brink) {
     return fuse_dispatch(L, brink, F.pitch, [&](auto, auto kernel) {
+        // the limit belongs to the kernel, not to the handle: the same for all of them
         return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, F.lds);
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, kFuseMaxLds);
     });
 }
 

@@ -66,7 +66,7 @@ inline hipError_t launch_fused_steps(const Layout&, const Ghosts&, const Fuse&, 
     return hipErrorNoDevice;
 }
 #else
-// Let the handle's kernel use fuse.lds bytes of LDS on the current device.
+// Let the handle's kernel use up to kFuseMaxLds bytes of LDS on the current device.
 hipError_t fuse_prepare(const Layout& L, const Fuse& F, bool brink);
 
 // fuse.steps time steps src -> dst in one launch; src's ghost slots hold the incoming

@@ -85,3 +85,16 @@ def test_set_objective_returns_with_its_tables_laid_out(stand_in):
         assert events()[last].endswith(" 16")
         assert "sync 16" in events()[last + 1:], events()
     """)
+
+
+def test_a_later_handle_leaves_the_lds_limit_of_an_earlier_one(stand_in):
+    """The limit on dynamic LDS is the kernel's, for every handle that uses it."""
+    _run(stand_in, """
+        limits = []
+        for g in (wl.pipe(X=23, Y=21, Z=37, r2=97.0), wl.closed_box(X=3, Y=5, Z=2)):
+            hip.stand_in_clear()
+            vessel(g)
+            limits.append([int(e.split()[-2]) for e in events() if e.startswith("attribute")])
+        first, second = limits
+        assert first and second and min(second) >= max(first), limits
+    """, HEMELB_FUSE="3,1,512,1")
