@@ -920,9 +920,11 @@ int do_step(hemelb_lb* h) {
     return HEMELB_OK;
 }
 
-// Called by every entry point that enqueues work on A: note whether it is captured.
+// Called by every entry point that enqueues work on A: note whether it is captured.  The
+// default stream cannot be, and to ask about it is an error while some other blocking
+// stream is being captured.
 int note_capture(hemelb_lb* h) {
-    if (h->fuse.steps == 0 || h->captured) return HEMELB_OK;
+    if (h->fuse.steps == 0 || h->captured || !h->stream) return HEMELB_OK;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(h->stream, &cap), "capture status");
     h->captured = cap != hipStreamCaptureStatusNone;

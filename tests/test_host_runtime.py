@@ -98,3 +98,20 @@ def test_a_later_handle_leaves_the_lds_limit_of_an_earlier_one(stand_in):
         first, second = limits
         assert first and second and min(second) >= max(first), limits
     """, HEMELB_FUSE="3,1,512,1")
+
+
+def test_calls_on_the_default_stream_do_not_ask_whether_it_is_captured(stand_in):
+    """The runtime answers that with an error while a blocking stream is being captured."""
+    _run(stand_in, """
+        g = wl.pipe()
+        h = vessel(g)
+        hip.stand_in_null_capture(906)  # hipErrorStreamCaptureImplicit
+        buf = np.zeros((15, g.n_sites), dtype=np.float32)
+        p = ctypes.c_void_p(buf.ctypes.data)
+        t = ctypes.c_int64(0)
+        L.check(lib.hemelb_lb_step(h, 5))
+        L.check(lib.hemelb_lb_observables(h, p, None, None))
+        L.check(lib.hemelb_lb_get_state(h, p, ctypes.byref(t)))
+        L.check(lib.hemelb_lb_set_state(h, p, 0))
+        assert t.value == 5
+    """)
