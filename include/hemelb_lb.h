@@ -237,8 +237,9 @@ int hemelb_lb_destroy(hemelb_lb_t h);
  * lattices one launch makes several steps where nothing asks for them one by one (a
  * record, kernel timing, a divergence check or the objective's window), with the same
  * results; a handle of which a call was captured into a graph steps one by one from
- * then on.  Once per 1024 steps a small kernel
- * tabulates the iolet time series.
+ * then on, and so does one whose device had no room for the third population buffer and
+ * the group data that this takes.  Once per 1024 steps a small kernel tabulates the iolet
+ * time series.
  * Errors: EINVAL (n < 0), EORDER (past the end of a record), ECANCELLED, EDEVICE.
  */
 int hemelb_lb_step(hemelb_lb_t h, int64_t n);
@@ -316,8 +317,8 @@ int hemelb_lb_info(hemelb_lb_t h, hemelb_lb_info_t* info);
 /*
  * Plan without a device: validate `d` exactly as hemelb_lb_create does and report
  * the layout it would build (host `info`: n_sites, n_ghosts, pitch, addressing,
- * bytes_per_update, and device_bytes = the device memory create would allocate;
- * time is 0).  Runs on the host only, so it also serves to size a run before a
+ * bytes_per_update, and device_bytes = the device memory create would allocate where
+ * there is room for several steps per launch; time is 0).  Runs on the host only, so it also serves to size a run before a
  * GPU is at hand.  Errors: those of hemelb_lb_create's validation (EINVAL, with
  * the same messages), ENOMEM.
  */

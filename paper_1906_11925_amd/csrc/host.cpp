@@ -1860,6 +1860,37 @@ int hemelb_lb_plan(const hemelb_lb_desc_t* d, hemelb_lb_info_t* info) {
     return no_throw([&] { return plan_impl(d, info); });
 }
 
+// What several steps per launch need beyond single steps.  Where the device has no room
+// for it the handle steps one by one.
+static int fuse_init(hemelb_lb* h, const HostPlan& P, size_t popbytes) {
+    if (P.fuse_steps == 0) return HEMELB_OK;
+    const int64_t before = h->device_bytes;
+    uint8_t* prev = nullptr;
+    int rc = dev_alloc(h, &prev, popbytes, "population buffer");
+    h->A_prev = prev;
+    if (!rc) rc = dev_upload(h, &h->f_hdr, P.fuse_hdr, "step groups");
+    if (!rc) rc = dev_upload(h, &h->f_list, P.fuse_list, "step group sites");
+    if (!rc) rc = dev_upload(h, &h->f_rows, P.fuse_rows, "step group rows");
+    if (!rc) rc = dev_upload(h, &h->f_frac, P.fuse_frac, "step group walls");
+    if (rc == HEMELB_ENOMEM) {
+        (void)hipGetLastError();  // leave no error for later calls
+        for (void** p : {&h->A_prev, (void**)&h->f_hdr, (void**)&h->f_list, (void**)&h->f_rows,
+                         (void**)&h->f_frac}) {
+            if (*p) (void)hipFree(*p);
+            *p = nullptr;
+        }
+        h->device_bytes = before;
+        return HEMELB_OK;
+    }
+    if (rc) return rc;
+    h->fuse = hlb::Fuse{h->f_hdr, h->f_list, reinterpret_cast<const uint4*>(h->f_rows), h->f_frac,
+                        (int32_t)(P.fuse_hdr.size() / hlb::kFuseHdr), P.fuse_steps,
+                        P.fuse_threads, P.fuse_pitch, P.fuse_lds};
+    for (const bool brink : {false, true})
+        HIP_TRY(hlb::fuse_prepare(h->layout(), h->fuse, brink), "several steps per launch");
+    return HEMELB_OK;
+}
+
 // Fill a new handle from plan P: everything of hemelb_lb_create after the handle
 // exists.  On failure h has been released.
 static int init_handle(hemelb_lb* h, hemelb_lb_t* out, const hemelb_lb_desc_t* d, HostPlan& P,
@@ -1955,30 +1986,6 @@ static int init_handle(hemelb_lb* h, hemelb_lb_t* out, const hemelb_lb_desc_t* d
     } else {
         TRY(dev_upload(h, &h->tbl, P.tbl, "neighbour table"));
     }
-    if (P.fuse_steps > 0) {
-        void* p = nullptr;
-        const hipError_t e = hipMalloc(&p, popbytes);
-        if (e != hipSuccess) {
-            release(h);
-            return hip_fail(e, "population buffer");
-        }
-        h->A_prev = p;
-        h->device_bytes += (int64_t)popbytes;
-        TRY(dev_upload(h, &h->f_hdr, P.fuse_hdr, "step groups"));
-        TRY(dev_upload(h, &h->f_list, P.fuse_list, "step group sites"));
-        TRY(dev_upload(h, &h->f_rows, P.fuse_rows, "step group rows"));
-        TRY(dev_upload(h, &h->f_frac, P.fuse_frac, "step group walls"));
-        h->fuse = hlb::Fuse{h->f_hdr, h->f_list, reinterpret_cast<const uint4*>(h->f_rows), h->f_frac,
-                            (int32_t)(P.fuse_hdr.size() / hlb::kFuseHdr), P.fuse_steps,
-                            P.fuse_threads, P.fuse_pitch, P.fuse_lds};
-        for (const bool brink : {false, true}) {
-            const hipError_t f = hlb::fuse_prepare(h->layout(), h->fuse, brink);
-            if (f != hipSuccess) {
-                release(h);
-                return hip_fail(f, "several steps per launch");
-            }
-        }
-    }
     TRY(dev_upload(h, &h->g_site, P.gsite, "ghost sites"));
     TRY(dev_upload(h, &h->g_dir, P.gdir, "ghost dirs"));
     TRY(dev_upload(h, &h->g_iolet, P.giol, "ghost iolets"));
@@ -2001,6 +2008,7 @@ static int init_handle(hemelb_lb* h, hemelb_lb_t* out, const hemelb_lb_desc_t* d
             return hip_fail(e, "flag init");
         }
     }
+    TRY(fuse_init(h, P, popbytes));  // last: what it needs is not needed to step
     const hlb::Layout L = h->layout();
     for (void* p : {h->A[0], h->A[1], h->A_prev}) {
         if (!p) continue;

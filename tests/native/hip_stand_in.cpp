@@ -8,6 +8,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <utility>
 
 namespace {
 
@@ -16,6 +17,7 @@ std::map<const void*, std::string> g_kernel;  // host stub -> kernel name
 std::map<void*, size_t> g_alloc;
 int64_t g_live = 0;                // bytes allocated
 int64_t g_limit = INT64_MAX;       // most bytes
+int g_error = 0;                   // what hipGetLastError returns and forgets
 int g_null_capture = 0;            // hipStreamIsCapturing's result for the default stream
 const char* g_watch = "";          // calls g_then in the g_watch_at-th launch of this kernel
 int g_watch_at = 0;
@@ -80,7 +82,7 @@ int hipFuncSetAttribute(const void* stub, int, int value) {
 
 // ---- memory -------------------------------------------------------------------
 int hipMalloc(void** p, size_t bytes) {
-    if (g_live + (int64_t)bytes > g_limit) return 2;  // hipErrorOutOfMemory
+    if (g_live + (int64_t)bytes > g_limit) return g_error = 2;  // hipErrorOutOfMemory
     *p = calloc(1, std::max<size_t>(bytes, 1));
     g_alloc[*p] = bytes;
     g_live += (int64_t)bytes;
@@ -112,7 +114,7 @@ int hipGetDevice(int* dev) {
 }
 int hipSetDevice(int) { return 0; }
 const char* hipGetErrorString(int e) { return e == 2 ? "out of memory" : "error of the stand-in"; }
-int hipGetLastError() { return 0; }
+int hipGetLastError() { return std::exchange(g_error, 0); }
 int hipDeviceSynchronize() { return 0; }
 int hipStreamSynchronize(void* stream) {
     event("sync", stream);

@@ -115,3 +115,34 @@ def test_calls_on_the_default_stream_do_not_ask_whether_it_is_captured(stand_in)
         L.check(lib.hemelb_lb_set_state(h, p, 0))
         assert t.value == 5
     """)
+
+
+def test_a_device_without_room_for_several_steps_per_launch(stand_in):
+    """Their third population buffer and groups are an extra: a handle that fits without
+    them is created, steps one by one and takes what it takes without them."""
+    _run(stand_in, """
+        g = wl.pipe()
+        os.environ["HEMELB_FUSE"] = "0"
+        h = vessel(g)
+        need = info(h).device_bytes
+        assert need == hip.stand_in_live()
+        L.check(lib.hemelb_lb_destroy(h))
+        del os.environ["HEMELB_FUSE"]
+        h = vessel(g)
+        full = info(h).device_bytes
+        assert full == hip.stand_in_live()
+        L.check(lib.hemelb_lb_destroy(h))
+        assert hip.stand_in_live() == 0 and full > need
+        for limit in (need, need + (full - need) // 2, full - 1, full):
+            hip.stand_in_limit(limit)
+            h = vessel(g)
+            fused = limit == full
+            assert info(h).device_bytes == hip.stand_in_live() == (full if fused else need)
+            hip.stand_in_clear()
+            hip.stand_in_limit(2 * full)  # the first step makes its table of iolet values
+            L.check(lib.hemelb_lb_step(h, 6))
+            assert len(launches("k_fused_steps")) == (2 if fused else 0)
+            assert len(launches("k_stream_collide")) == (0 if fused else 6)
+            L.check(lib.hemelb_lb_destroy(h))
+            assert hip.stand_in_live() == 0
+    """)
