@@ -90,9 +90,12 @@ constexpr int kStageChunks = kStageRows * kRowBytes / 16 + kStageRecs;  // <= th
 // source's first population row (tile * q * 64 + lane) from the group's base, plus one
 // row.  The base is the start of the buffer, or, for a lattice whose FP32 buffer
 // reaches past 4 GiB, 2^29 elements below the group's first tile (the host marks a
-// group whose sources lie outside that window).
+// group whose sources lie outside that window).  The window ends 128 KB below 4 GiB, more
+// than the widest staged workgroup holds (16 tiles of D3Q19: 77 KB), so that a reference
+// below the workgroup's own populations, taken from their start, wraps to more than they
+// hold.
 constexpr int64_t kRefBack = (int64_t)1 << 29;
-constexpr int64_t kRefSpan = ((int64_t)1 << 30) - 4096;  // references stay below 2^30
+constexpr int64_t kRefSpan = ((int64_t)1 << 30) - ((int64_t)1 << 15);
 inline __host__ __device__ int64_t group_base(bool wide, int32_t tile, int q) {
     const int64_t at = (int64_t)tile * q * kTile;
     return wide && at > kRefBack ? at - kRefBack : 0;

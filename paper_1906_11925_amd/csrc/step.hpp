@@ -282,6 +282,8 @@ __device__ inline void stream_collide_staged(const typename Store<ST>::T* __rest
     using T = typename Store<ST>::T;
     using C = Codec<Q, ST, SC>;
     constexpr int SZ = sizeof(T), kRow = kRowSize<SZ>, kTileBytes = Q * kRow;
+    static_assert(W * kTileBytes + kRow <= ((int64_t)1 << 32) - kRefSpan * 4,
+                  "a reference below lo must not wrap into the span");
     if (((int64_t)T0 << kTileShift) >= n) return;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> kTileShift);
     const int lane = (int)threadIdx.x & (kTile - 1);
