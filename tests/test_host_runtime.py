@@ -146,3 +146,41 @@ def test_a_device_without_room_for_several_steps_per_launch(stand_in):
             L.check(lib.hemelb_lb_destroy(h))
             assert hip.stand_in_live() == 0
     """)
+
+
+@pytest.mark.parametrize("form,singles", [("0", 12), ("2,1,512,0", 0), ("3,1,512,1", 0)])
+def test_launches_of_a_step_request(stand_in, form, singles):
+    _run(stand_in, f"""
+        h = vessel(wl.pipe())
+        L.check(lib.hemelb_lb_step(h, 12))
+        steps = int(os.environ["HEMELB_FUSE"][0])
+        assert len(launches("k_stream_collide")) == {singles}
+        assert len(launches("k_fused_steps")) == (12 // steps if steps else 0)
+    """, HEMELB_FUSE=form)
+
+
+@pytest.mark.parametrize("form", ["2,1,512,0", "3,1,512,1"])
+@pytest.mark.parametrize("after", [1, 2, 5])
+def test_cancel_between_launches_of_several_steps(stand_in, form, after):
+    """A launch that another was to follow keeps no state before its last step, so a request
+    that is cancelled behind it makes one more, single step: the outputs need that state."""
+    _run(stand_in, f"""
+        steps = int(os.environ["HEMELB_FUSE"][0])
+        h = vessel(wl.pipe())
+        cancel = THEN(lambda: lib.hemelb_lb_cancel(h) and None)
+        hip.stand_in_at_launch(b"k_fused_steps", {after}, cancel)
+        rc = lib.hemelb_lb_step(h, 20)
+        assert rc == L.HEMELB_ECANCELLED, L.last_error()
+        assert len(launches("k_fused_steps")) == {after} and len(launches("k_stream_collide")) == 1
+        assert launches("k_stream_collide")[0] > launches("k_fused_steps")[-1]
+        assert info(h).time == {after} * steps + 1
+        assert f"cancelled after {{info(h).time}} of 20" in L.last_error()
+        L.check(lib.hemelb_lb_step(h, steps))
+        assert info(h).time == {after} * steps + 1 + steps
+        # behind the last launch of a request nothing is missing
+        hip.stand_in_clear()
+        hip.stand_in_at_launch(b"k_fused_steps", 1, cancel)
+        assert lib.hemelb_lb_step(h, steps) == 0
+        assert lib.hemelb_lb_step(h, 1) == L.HEMELB_ECANCELLED
+        assert not launches("k_stream_collide")
+    """, HEMELB_FUSE=form)
