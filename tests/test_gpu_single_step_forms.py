@@ -1,6 +1,6 @@
 """The forms of the single step give the same bits, with several steps per launch off.
 
-Lattices below 2^18 sites make several steps per launch by default, in a kernel that knows
+Small lattices make several steps per launch by default, in a kernel that knows
 neither the addressing nor the staging of the single step.  Here HEMELB_FUSE=0 turns that
 off, so that every step is one launch of the form under test: the staged copies of 4, 8 and
 16 tiles, by loads that write LDS directly and through registers, in every storage; the

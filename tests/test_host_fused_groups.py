@@ -7,7 +7,9 @@ has neither the third population buffer nor the groups' data.
 import numpy as np
 import pytest
 
-from paper_1906_11925_amd import plan
+import workloads as wl
+from paper_1906_11925_amd import links, plan
+from paper_1906_11925_amd.lb import lattice_vectors
 
 
 def _opp(i):
@@ -47,4 +49,43 @@ def test_codes_of_a_row_stay_within_16_bits(monkeypatch, grandchildren, fits):
     nbr = _star(19, 13, grandchildren, 140096)
     single = _bytes(monkeypatch, nbr, "0", lattice=19)
     assert (_bytes(monkeypatch, nbr, "2,8,1024,2", lattice=19) > single) == fits
-    assert (_bytes(monkeypatch, nbr, None, lattice=19) > single) == fits
+
+
+def _pipe(radius, length):
+    w = 2 * int(np.ceil(radius)) + 3
+    return wl.pipe(X=w, Y=w, Z=length, r2=radius ** 2)
+
+
+GEOMS = {
+    "pipe13k": wl.pipe,
+    "pipe75k": lambda: _pipe(16.0, 94),
+    "aneurysm_half": lambda: wl.aneurysm(half=True),
+    "tree230k": lambda: wl.tree(170, 21.5, (85.0, 85.0, 10.75), 6, seed=5),
+    "pipe255k": lambda: _pipe(23.0, 154),
+}
+
+
+# measured on the GPU: where several steps per launch are faster than single ones
+@pytest.mark.parametrize("name,q,storage,bfl,several", [
+    ("pipe13k", 15, "f32", False, True),
+    ("pipe13k", 19, "bf16", True, True),
+    ("pipe75k", 19, "f32", False, True),
+    ("pipe75k", 15, "f32", True, True),
+    ("pipe75k", 19, "f32", True, False),
+    ("aneurysm_half", 15, "f32", False, True),
+    ("aneurysm_half", 15, "f16", False, True),
+    ("aneurysm_half", 19, "f32", False, False),
+    ("aneurysm_half", 19, "f16", False, True),
+    ("tree230k", 15, "f32", False, False),
+    ("tree230k", 15, "f16", False, True),
+    ("tree230k", 19, "f16", False, False),
+    ("pipe255k", 15, "f32", False, False),
+    ("pipe255k", 15, "bf16", False, False),
+    ("pipe255k", 19, "f32", False, False),
+])
+def test_default_choice(monkeypatch, name, q, storage, bfl, several):
+    g = GEOMS[name]()
+    coords, nbr = links(g.labels, g.shape, g.periodic, q)
+    kw = dict(lattice=q, storage=storage, coords=coords, iolets=list(g.iolets),
+              wall_q=g.wall_fractions(lattice_vectors(q)) if bfl else None)
+    assert (_bytes(monkeypatch, nbr, None, **kw) > _bytes(monkeypatch, nbr, "0", **kw)) == several
