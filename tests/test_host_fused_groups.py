@@ -89,3 +89,39 @@ def test_default_choice(monkeypatch, name, q, storage, bfl, several):
     kw = dict(lattice=q, storage=storage, coords=coords, iolets=list(g.iolets),
               wall_q=g.wall_fractions(lattice_vectors(q)) if bfl else None)
     assert (_bytes(monkeypatch, nbr, None, **kw) > _bytes(monkeypatch, nbr, "0", **kw)) == several
+
+
+@pytest.mark.parametrize("form", ["2,8,1024,0", "2,3,512,1", "3,4,128,1", "4,6,512,2"])
+@pytest.mark.parametrize("q", [15, 19])
+def test_groups_hold_as_many_tiles_as_fit(monkeypatch, q, form):
+    """The plan's bytes are those of groups grown here by definition: whole tiles, as many as
+    leave the inner sites within a row and a site a thread (fewer than 2048 sites, which one
+    task plans, in the caller's order)."""
+    steps, tiles, threads, row = (int(x) for x in form.split(","))
+    g = wl.pipe(X=13, Y=12, Z=19, r2=29.0)
+    _, nbr = links(g.labels, g.shape, g.periodic, q)
+    n = len(nbr)
+    assert 1024 < n < 2048
+    pitch = (2048, 3072, 4096 if q == 15 else 3584)[row] // 4
+
+    def grow(a, b):
+        inside, counts = set(range(64 * a, min(n, 64 * b))), []
+        for _ in range(steps):
+            counts.append(len(inside))
+            inside |= {int(v) for s in inside for v in nbr[s, 1:] if v >= 0}
+        return counts + [len(inside)]
+
+    words, t, fits = 0, 0, True
+    while 64 * t < n and fits:
+        for take in range(min(tiles, (n + 63) // 64 - t), 0, -1):
+            c = grow(t, t + take)
+            fits = c[steps - 1] <= pitch and (steps == 2 or c[steps - 2] <= threads)
+            if fits:
+                break
+        words += 16 + c[steps] + c[steps - 1] * (8 if q == 15 else 12)
+        t += take
+    kw = dict(lattice=q, iolets=list(g.iolets))
+    single = _bytes(monkeypatch, nbr, "0", **kw)
+    monkeypatch.setenv("HEMELB_FUSE", form)
+    info = plan(nbr, 0.8, **kw)
+    assert info["device_bytes"] - single == (q * info["pitch"] * 4 + 4 * words if fits else 0)
