@@ -366,8 +366,8 @@ int hemelb_lb_kernel_time(hemelb_lb_t h, double* ms, int64_t* launches);
  * Errors: EINVAL if the handle was created without coords, for a NULL pointer,
  * width or height outside [1, 16384], steps outside [0, 2^24], an unknown filter
  * or a non-finite scale or offset; ENOMEM; EDEVICE.  The first call builds the
- * block maps of the volume (device memory: about 5 bytes per 4x4x4 block of the
- * sites' bounding box).
+ * block maps of the volume (device memory: about 6 bytes per 4x4x4 block of the
+ * sites' bounding box, and 2 more while they are built).
  */
 #define HEMELB_VIEW_FIX (1 << 20)
 #define HEMELB_FILTER_NEAREST 0
