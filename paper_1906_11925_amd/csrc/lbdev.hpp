@@ -410,7 +410,7 @@ __device__ inline void staged_refs(const Table& tb, const StageHdr& h, int t, ui
 
 // As staged_refs, but the links themselves (sites, walls, ghost slots), for groups whose
 // sources lie too far apart for 32-bit references.  8% of the groups of a 395M-site tree
-// are such: with the global records for them its step took 11.15 ms, so 9.25.
+// are such: with the global records for them its step took 11.15 ms, so 9.08.
 template <int Q>
 __device__ inline void staged_slots(const Table& tb, const StageHdr& h, int t, const StageLds& lds,
                                     const LinkLds<Q>& links, int32_t (&j)[Q]) {
