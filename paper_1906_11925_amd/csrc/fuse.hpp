@@ -28,7 +28,7 @@ constexpr int kFuseHdr = 16;           // 32-bit words per group header
 //      site's own opposite population), P + x for an iolet link.  The outermost sites
 //      (from count[steps - 1], only ever read from global memory) count from
 //      count[steps - 1] + gap, gap = P where they would pass P, so that no code of a
-//      site reads as another's wall;
+//      site reads as another's wall (the host builds no group whose codes pass 16 bits);
 //      then the first iolet link and the mask of the iolet directions (D3Q15: link << 14
 //      | mask >> 1 in one word; D3Q19: two words), and with interpolated walls the entry
 //      of the site in frac (-1: none);

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kScBlock) void k_stream_collide(
 }
 
 // workgroups of W tiles with their own populations staged in LDS (block addressing);
-// DMA: the copy writes LDS directly (FP32); FOUT: also store the pulled populations
+// DMA: the copy writes LDS directly; FOUT (FP32): also store the pulled populations
 template <int Q, int ST, bool SC, bool BRINK, int W, bool DMA, bool FOUT>
 __global__ __launch_bounds__(W * kTile) void k_stream_collide_staged(
     const typename Store<ST>::T* __restrict__ src, typename Store<ST>::T* __restrict__ dst,
@@ -131,13 +131,12 @@ __global__ __launch_bounds__(kBlock) void k_ghost_fill(typename Store<ST>::T* __
 // ---------------------------------------------------------------------------
 // Bound by requests between L1 and L2, its stores more than its gathers as long as they
 // went out a block's z-run at a time (16 bytes).  ORDER: a workgroup takes a chunk of
-// sites and puts the results into the caller's order in LDS before
-// it stores them (5.6M sites, with the site order of the step before it: FP32 214 -> 184
-// us, FP16 178 -> 152 us; 20.8M sites 833 -> 590 us; two passes of 512 threads took 221
-// and 185 us; the bound on registers keeps two workgroups on a compute unit).  Otherwise
-// one group, stored as it
-// lies: small lattices, where the few large workgroups leave the chip idle, and D3Q19,
-// whose registers do not fit the bound (5.6M sites FP16: 184 us, in order 219 us).
+// sites and puts the results into the caller's order in LDS before it stores them (5.6M
+// sites, with the site order of the step before it: FP32 214 -> 184 us, FP16 178 -> 152 us;
+// 20.8M sites 833 -> 590 us; half as many threads in two passes took 221 and 185 us; the
+// bound on registers keeps two workgroups on a compute unit).  Otherwise one group, stored
+// as it lies: small lattices, where the few large workgroups leave the chip idle, and
+// D3Q19, whose registers do not fit the bound (5.6M sites FP16: 184 us, in order 219 us).
 constexpr int kObsThreads = kChunk;
 
 template <int Q, int ST, bool SC, bool ORDER>
@@ -162,96 +161,98 @@ __global__ __launch_bounds__(ORDER ? kObsThreads : kBlock, ORDER ? 8 : 4) void k
     const int t = tid & (kBlock - 1);
     const bool blocks = streamed && tb.grp;
     if (blocks) stage_links<Q>(wave, tid & (kTile - 1), links);
+    // one pass (kSites sites at a site a thread), yet written as a loop: straight code spills
+    // no register but orders the loads otherwise and takes 188 us instead of 184 (5.6M sites)
 #pragma unroll 1
     for (int k0 = 0; k0 < kSites; k0 += kThreads) {
-    const int32_t s = first + k0 + tid, g = (first + k0) / kBlock + (wave >> 2);
-    const bool live = (s & ~(kTile - 1)) < n, mine = s < n;
-    StageLds& group = lds[wave >> 2];
-    StageHdr h{0, 0, 0, false};
-    if (blocks) {
-        if (k0 > 0) __syncthreads();  // the records before are done with
-        if ((int64_t)g * kBlock < n) h = stage_header(tb, g);
-        if (h.nown > 0) stage(tb, h, g, t, group);
-        lds_loads_done();
-        __syncthreads();
-    }
-    float d[Q];
-    if (h.nown > 0) {
-        if (mine) {
-            const int64_t base = group_base(tb.wide, 4 * g, Q);
-            const uint32_t own = slot_ref<Q, SZ>(s, (uint32_t)base);
-            uint32_t e[Q], gmask;
-            staged_refs<Q, SZ>(tb, h, t, (uint32_t)base, own, group, links, e, gmask);
-            refs_gather<Q, ST, SC>(A, base, own, e, d);
+        const int32_t s = first + k0 + tid, g = (first + k0) / kBlock + (wave >> 2);
+        const bool live = (s & ~(kTile - 1)) < n, mine = s < n;
+        StageLds& group = lds[wave >> 2];
+        StageHdr h{0, 0, 0, false};
+        if (blocks) {
+            if (k0 > 0) __syncthreads();  // the records before are done with
+            if ((int64_t)g * kBlock < n) h = stage_header(tb, g);
+            if (h.nown > 0) stage(tb, h, g, t, group);
+            lds_loads_done();
+            __syncthreads();
         }
-    } else {
-        int32_t j[Q];
-        if (streamed && live) links_wave<Q, false>(tb, s, j);
-        if (mine) {
-            d[0] = C::dec(0, A[tix<Q>(0, s)]);
-#pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                int dir = i;
-                int32_t site = s;
-                if (streamed) link_src(i, j[i], s, dir, site);
-                d[i] = C::dec(i, A[tix<Q>(dir, site)]);
+        float d[Q];
+        if (h.nown > 0) {
+            if (mine) {
+                const int64_t base = group_base(tb.wide, 4 * g, Q);
+                const uint32_t own = slot_ref<Q, SZ>(s, (uint32_t)base);
+                uint32_t e[Q], gmask;
+                staged_refs<Q, SZ>(tb, h, t, (uint32_t)base, own, group, links, e, gmask);
+                refs_gather<Q, ST, SC>(A, base, own, e, d);
             }
-            if (streamed) apply_bfl<Q, ST, SC>(A, s, n, j, d);
-        }
-    }
-    float op = 0.f, ux = 0.f, uy = 0.f, uz = 0.f, ow = 0.f;
-    if (mine) {
-        float drho, mx, my, mz;
-        moments<Q>(d, drho, mx, my, mz);
-        const float rho = 1.0f + drho;
-        const float ir = 1.0f / rho;
-        ux = mx * ir;
-        uy = my * ir;
-        uz = mz * ir;
-        op = drho * (1.0f / 3.0f);
-        const float nx = wss ? normal[s] : 0.f, ny = wss ? normal[n + s] : 0.f,
-                    nz = wss ? normal[2 * (int64_t)n + s] : 0.f;
-        if (nx != 0.f || ny != 0.f || nz != 0.f) {
-            float deq[Q];
-            eq_dev<Q>(drho, rho, ux, uy, uz, deq);
-            float pxx = 0, pyy = 0, pzz = 0, pxy = 0, pxz = 0, pyz = 0;
+        } else {
+            int32_t j[Q];
+            if (streamed && live) links_wave<Q, false>(tb, s, j);
+            if (mine) {
+                d[0] = C::dec(0, A[tix<Q>(0, s)]);
 #pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                const float e = d[i] - deq[i];
-                const float cx = Lt::cx[i], cy = Lt::cy[i], cz = Lt::cz[i];
-                if (Lt::cx[i]) pxx += e;
-                if (Lt::cy[i]) pyy += e;
-                if (Lt::cz[i]) pzz += e;
-                if (Lt::cx[i] && Lt::cy[i]) pxy += cx * cy * e;
-                if (Lt::cx[i] && Lt::cz[i]) pxz += cx * cz * e;
-                if (Lt::cy[i] && Lt::cz[i]) pyz += cy * cz * e;
+                for (int i = 1; i < Q; ++i) {
+                    int dir = i;
+                    int32_t site = s;
+                    if (streamed) link_src(i, j[i], s, dir, site);
+                    d[i] = C::dec(i, A[tix<Q>(dir, site)]);
+                }
+                if (streamed) apply_bfl<Q, ST, SC>(A, s, n, j, d);
             }
-            const float k = -(1.0f - 0.5f * omega);
-            const float sx = k * (pxx * nx + pxy * ny + pxz * nz);
-            const float sy = k * (pxy * nx + pyy * ny + pyz * nz);
-            const float sz = k * (pxz * nx + pyz * ny + pzz * nz);
-            const float nsn = sx * nx + sy * ny + sz * nz;
-            const float tx = sx - nsn * nx, ty = sy - nsn * ny, tz = sz - nsn * nz;
-            ow = sqrtf(tx * tx + ty * ty + tz * tz);
         }
-    }
-    if constexpr (ORDER) {
-        out[0][k0 + tid] = op;
-        out[1][k0 + tid] = ux;
-        out[2][k0 + tid] = uy;
-        out[3][k0 + tid] = uz;
-        out[4][k0 + tid] = ow;
-    } else if (mine) {
-        const int32_t o = perm ? perm[s] : s;
-        if (p) p[o] = op;
-        if (u) {
-            float* const uo = u + 3 * (int64_t)o;
-            uo[0] = ux;
-            uo[1] = uy;
-            uo[2] = uz;
+        float op = 0.f, ux = 0.f, uy = 0.f, uz = 0.f, ow = 0.f;
+        if (mine) {
+            float drho, mx, my, mz;
+            moments<Q>(d, drho, mx, my, mz);
+            const float rho = 1.0f + drho;
+            const float ir = 1.0f / rho;
+            ux = mx * ir;
+            uy = my * ir;
+            uz = mz * ir;
+            op = drho * (1.0f / 3.0f);
+            const float nx = wss ? normal[s] : 0.f, ny = wss ? normal[n + s] : 0.f,
+                        nz = wss ? normal[2 * (int64_t)n + s] : 0.f;
+            if (nx != 0.f || ny != 0.f || nz != 0.f) {
+                float deq[Q];
+                eq_dev<Q>(drho, rho, ux, uy, uz, deq);
+                float pxx = 0, pyy = 0, pzz = 0, pxy = 0, pxz = 0, pyz = 0;
+#pragma unroll
+                for (int i = 1; i < Q; ++i) {
+                    const float e = d[i] - deq[i];
+                    const float cx = Lt::cx[i], cy = Lt::cy[i], cz = Lt::cz[i];
+                    if (Lt::cx[i]) pxx += e;
+                    if (Lt::cy[i]) pyy += e;
+                    if (Lt::cz[i]) pzz += e;
+                    if (Lt::cx[i] && Lt::cy[i]) pxy += cx * cy * e;
+                    if (Lt::cx[i] && Lt::cz[i]) pxz += cx * cz * e;
+                    if (Lt::cy[i] && Lt::cz[i]) pyz += cy * cz * e;
+                }
+                const float k = -(1.0f - 0.5f * omega);
+                const float sx = k * (pxx * nx + pxy * ny + pxz * nz);
+                const float sy = k * (pxy * nx + pyy * ny + pyz * nz);
+                const float sz = k * (pxz * nx + pyz * ny + pzz * nz);
+                const float nsn = sx * nx + sy * ny + sz * nz;
+                const float tx = sx - nsn * nx, ty = sy - nsn * ny, tz = sz - nsn * nz;
+                ow = sqrtf(tx * tx + ty * ty + tz * tz);
+            }
         }
-        if (wss) wss[o] = ow;
-    }
+        if constexpr (ORDER) {
+            out[0][k0 + tid] = op;
+            out[1][k0 + tid] = ux;
+            out[2][k0 + tid] = uy;
+            out[3][k0 + tid] = uz;
+            out[4][k0 + tid] = ow;
+        } else if (mine) {
+            const int32_t o = perm ? perm[s] : s;
+            if (p) p[o] = op;
+            if (u) {
+                float* const uo = u + 3 * (int64_t)o;
+                uo[0] = ux;
+                uo[1] = uy;
+                uo[2] = uz;
+            }
+            if (wss) wss[o] = ow;
+        }
     }
     if constexpr (ORDER) {
         __syncthreads();
