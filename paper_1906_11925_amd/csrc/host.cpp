@@ -735,7 +735,7 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
     const bool wide = wide_buffers(n + P.ncells, q);
     const int64_t groups = (ttiles + 3) / 4;
     P.grp.assign((size_t)groups * 2, 0);
-    std::vector<int32_t> recs;
+    std::vector<int32_t> recs, past;  // blocks of the records, those of them with ghost cells
     std::vector<uint16_t> rows;  // byte offsets into the records
     constexpr int kRowLen = hlb::kRowBytes / 2;
     for (int64_t g = 0; g < groups; ++g) {
@@ -768,12 +768,15 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
                 rows[(size_t)k * kRowLen + dd] =
                     (uint16_t)(nown * hlb::kRowBytes + idx * sizeof(hlb::BlockRec));
             }
+        past.clear();
+        for (const int32_t b : recs)
+            if (b >= 0 && P.rec[b].goff >= 0) past.push_back(b);
+        fits = fits && nown * hlb::kRowBytes / 16 + (int)(recs.size() + past.size()) <= hlb::kStageChunks;
         if (!fits) {
             P.fallback_bytes += global_bytes;
             continue;
         }
         // references of a wide lattice are offsets within a window around the group
-        bool ghosts = false;
         const int64_t base = hlb::group_base(wide, (int32_t)(4 * g), q);
         auto inside = [&](int64_t slot) {
             const int64_t e = (slot / hlb::kTile) * q * hlb::kTile - base;
@@ -784,23 +787,29 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
             fits = fits && (rec_mask(P.rec[b]) == 0 ||
                             (inside(P.rec[b].off) && inside(P.rec[b].off + hlb::kTile - 1)));
             if (P.rec[b].goff < 0) continue;
-            ghosts = true;
             fits = fits && inside(n) && inside(n + P.rec[b].goff + hlb::kTile - 1);
         }
         const size_t row_words = (size_t)nown * hlb::kRowBytes / 4;
         const size_t at = P.blob.size();
-        P.blob.resize(at + row_words + recs.size() * 4, 0);
+        const size_t nrec = recs.size() + past.size();
+        P.blob.resize(at + row_words + nrec * 4, 0);
         std::memcpy(&P.blob[at], rows.data(), rows.size() * 2);
-        for (size_t r = 0; r < recs.size(); ++r) {
+        for (size_t r = 0, gr = recs.size(); r < recs.size(); ++r) {
             hlb::BlockRec c{0u, 0u, 0, -1};  // no block there: no fluid, no ghost cells
             if (recs[r] >= 0) {
                 c = P.rec[recs[r]];
                 c.off -= 1;
-                c.goff = c.goff >= 0 ? recs[r] : -1;  // staged copies name ghost blocks by id
+                if (c.goff >= 0) {
+                    const uint64_t gm = P.gmask[recs[r]];
+                    const hlb::BlockRec ghost{(uint32_t)gm, (uint32_t)(gm >> 32),
+                                              (int32_t)n + c.goff - 1, -1};
+                    std::memcpy(&P.blob[at + row_words + 4 * gr], &ghost, sizeof ghost);
+                    c.goff = (int32_t)(nown * hlb::kRowBytes + gr++ * sizeof(hlb::BlockRec));
+                }
             }
             std::memcpy(&P.blob[at + row_words + 4 * r], &c, sizeof c);
         }
-        P.grp[2 * g + 1] = nown | (int32_t)(recs.size() << 16) | (ghosts ? hlb::kGroupGhosts : 0) |
+        P.grp[2 * g + 1] = nown | (int32_t)(nrec << 16) | (past.empty() ? 0 : hlb::kGroupGhosts) |
                            (fits ? 0 : hlb::kGroupFar);
     }
     if (P.blob.empty()) P.blob.assign(4, 0);
@@ -839,8 +848,11 @@ bool build_blocks(const hemelb_lb_desc_t* d, const HostLat& lat, const std::vect
                 int32_t got = (int32_t)0x80000000u;
                 if ((mk >> pp) & 1ull)
                     got = r.off + 1 + __builtin_popcountll(mk & below);
-                else if (r.goff >= 0 && ((P.gmask[r.goff] >> pp) & 1ull))
-                    got = (int32_t)n + P.rec[r.goff].goff + __builtin_popcountll(P.gmask[r.goff] & below);
+                else if (r.goff >= 0) {
+                    const hlb::BlockRec& c = *reinterpret_cast<const hlb::BlockRec*>(bytes + r.goff);
+                    const uint64_t gm = rec_mask(c);
+                    if ((gm >> pp) & 1ull) got = c.off + 1 + __builtin_popcountll(gm & below);
+                }
                 if (got != want) {
                     int64_t none = -1;
                     bad.compare_exchange_strong(none, s * q + i);

@@ -58,9 +58,10 @@ struct BlockRec {
 //    from the block of its first site; row k, 16-bit entry d = byte offset in the
 //    blob of the record of neighbour d of own block k; where no block exists it names an
 //    empty record (no fluid, no ghost cells)),
-//    then nrec BlockRecs whose first nown are the own blocks in order; in these
-//    copies off is one less and goff holds the block's id when it has ghost cells
-//    (-1 otherwise).
+//    then nrec BlockRecs.  The first nown are the own blocks in order; in these
+//    copies off is one less, and goff of a block with ghost cells (-1 otherwise) is the
+//    byte offset in the blob of its ghost record, which holds gmask and, in off, the slot
+//    of its first ghost cell less one.  The ghost records come last.
 struct Table {
     const int32_t* t32;
     const uint16_t* t16;

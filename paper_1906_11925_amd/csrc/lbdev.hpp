@@ -299,6 +299,11 @@ __device__ inline StageHdr stage_header(const Table& tb, int32_t g) {
                     far ? cnt & 0xff : 0};
 }
 
+// Iolet links whose data are loaded together: of each, a chain of dependent loads.  More at a
+// time cost registers that all sites pay for (D3Q15 FP32 staged 55 VGPRs, 60 with 5, 78 with
+// all 14; D3Q19 69, 75 with 5, which is a wave less per SIMD).
+constexpr int kLinkBatch = 3;
+
 // bytes of one population row of a tile
 template <int SZ>
 constexpr int kRowSize = kTile * SZ;
@@ -398,11 +403,12 @@ __device__ inline void staged_refs(const Table& tb, const StageHdr& h, int t, ui
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
         if (e[i] != own + (opp(i) - i) * kRowSize<SZ>) continue;
-        const int32_t b = (int32_t)rec(i).w;  // block with ghost cells
-        if (b < 0) continue;
-        const uint64_t gm = tb.gmask[b] << (lk[i - 1] & 63u);
+        const int32_t at = (int32_t)rec(i).w;  // the block's ghost record
+        if (at < 0) continue;
+        const uint4 g = *reinterpret_cast<const uint4*>(raw + at);
+        const uint64_t gm = (((uint64_t)g.y << 32) | g.x) << (lk[i - 1] & 63u);
         if ((int64_t)gm < 0) {
-            e[i] = slot_ref<Q, SZ>(tb.n + tb.brec[b].goff + __popcll(gm) - 1, base);
+            e[i] = slot_ref<Q, SZ>((int32_t)g.z + __popcll(gm), base);
             gmask |= 1u << i;
         }
     }
@@ -425,8 +431,9 @@ __device__ inline void staged_slots(const Table& tb, const StageHdr& h, int t, c
         const uint64_t m = (((uint64_t)r.y << 32) | r.x) << (l & 63u);
         j[i] = (int64_t)m < 0 ? (int32_t)r.z + __popcll(m) : (int32_t)0x80000000u;
         if (!h.ghosts || (int64_t)m < 0 || (int32_t)r.w < 0) continue;
-        const uint64_t gm = tb.gmask[r.w] << (l & 63u);
-        if ((int64_t)gm < 0) j[i] = tb.n + tb.brec[r.w].goff + __popcll(gm) - 1;
+        const uint4 g = *reinterpret_cast<const uint4*>(raw + (int32_t)r.w);
+        const uint64_t gm = (((uint64_t)g.y << 32) | g.x) << (l & 63u);
+        if ((int64_t)gm < 0) j[i] = (int32_t)g.z + __popcll(gm);
     }
 }
 
@@ -505,11 +512,11 @@ __device__ inline int64_t ghost_link(const Ghosts& G, int32_t n, int32_t slot, i
 template <int Q, int SZ>
 __device__ inline int64_t staged_link(const Ghosts& G, int32_t n, int64_t base,
                                       const uint32_t (&e)[Q], uint32_t lo, uint32_t gmask) {
-    int64_t l = -1;
+    const int first = __builtin_ctz(gmask);
+    uint32_t ref = 0;
 #pragma unroll
-    for (int i = 1; i < Q; ++i)
-        if (l < 0 && (gmask & (1u << i))) l = ghost_link<Q>(G, n, ref_slot<Q, SZ>(e[i] + lo, base), i);
-    return l;
+    for (int i = 1; i < Q; ++i) ref = i == first ? e[i] + lo : ref;
+    return ghost_link<Q>(G, n, ref_slot<Q, SZ>(ref, base), first);
 }
 
 // moments of FP32 deviations: drho = sum d, m = sum c d (constant-folded per lattice)
