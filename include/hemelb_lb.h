@@ -220,8 +220,8 @@ int hemelb_lb_links(const uint8_t* labels, const int32_t shape[3], const int32_t
  *                          that write LDS directly
  *   HEMELB_FUSE=K,W,T,R    make K (2 to 4) steps per launch in workgroups of up to W tiles
  *                          and T threads with LDS rows of class R (0 to 2); 0 never
- *                          (default: lattices of up to 221184 sites, 16-bit storage
- *                          245760; D3Q19 131072 and 212992; with wall_q 80000, D3Q19 65536)
+ *                          (default: by the sites, lattice, storage and walls, where it
+ *                          measured faster; none above 221184 sites)
  *   HEMELB_VERBOSE=1       print the time of each setup phase to stderr
  */
 int hemelb_lb_create(hemelb_lb_t* out, const hemelb_lb_desc_t* desc);

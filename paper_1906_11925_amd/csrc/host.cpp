@@ -1173,22 +1173,22 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
 }
 
 // Whether and how steps are fused: where a launch's latencies and not its bytes are the
-// cost.  Us a step, single / in the form chosen, vessels that are straight pipes unless
-// named:
-//   3 steps, 1 tile a group, up to 2^14 sites: 4k 8.4 / 4.4, 13k 8.5 / 4.2 (D3Q19 9.1 /
-//     4.4, FP16 8.6 / 4.7), 16k 8.9 / 4.4 (two steps 4.9); the two meet at 30k (5.2)
-//   2 steps, 2 tiles, up to 80000: 20k 9.0 / 5.0, 30k 8.8 / 5.2 (D3Q19 9.5 / 5.6), 75k
-//     9.8 / 6.3 (D3Q19 10.9 / 8.2)
-//   2 steps, 4 tiles: 100k 10.2 / 6.6 (D3Q19 11.0 / 8.8), 122k tree 10.4 / 7.2 (D3Q19 11.5
-//     / 9.8, FP16 11.7 / 9.5), 140k 10.2 / 8.9, 165k tree 11.1 / 10.1 (8 tiles 10.7)
-//   2 steps, 8 tiles where all groups then run at once (two per compute unit): from 172k
-//     sites on, 178k 10.8 / 9.9 (4 tiles 10.3), 200k aneurysm 10.4 / 8.7 (FP16 10.3 / 6.6),
-//     218k 11.6 / 10.8; D3Q19 FP16 from 2^17 on, 140k 11.5 / 10.5, 200k aneurysm 11.3 / 8.8
-// and not where the sites around the groups cost more than the launches: D3Q15 FP32 230k
-// tree 11.9 / 12.6, 255k 12.2 / 13.3; FP16 255k 11.6 / 12.4 (230k tree 11.7 / 11.2);
-// D3Q19 FP32 160k 11.7 / 12.9, 200k aneurysm 11.9 / 12.7, 255k 14.6 / 17.5; D3Q19 FP16 218k
-// 12.8 / 14.0; nor in 4 tiles above 172k with FP32, 205k 11.2 / 12.0.  Interpolated walls: 13k
-// 7.4 / 5.4, 53k 8.2 / 7.1 (D3Q19 9.2 / 7.9), 75k 8.8 / 8.0, not D3Q19 75k 9.9 / 10.0.
+// cost.  Us a step, single / in the form chosen, of straight pipes unless named:
+//   3 steps, 1 tile a group, up to 2^14 sites: 4k 7.3 / 4.4, 13k 7.5 / 4.2 (D3Q19 8.2 /
+//     4.4, FP16 7.8 / 4.7), 16k 7.8 / 4.5 (two steps 4.9); the two meet at 30k (5.2)
+//   2 steps, 2 tiles, up to 80000: 20k 7.8 / 5.0, 30k 7.7 / 5.2 (D3Q19 8.3 / 5.6), 75k
+//     8.7 / 6.4 (D3Q19 9.6 / 8.4)
+//   2 steps, 4 tiles: 100k 8.9 / 6.7 (D3Q19 9.7 / 9.0), 122k tree 8.8 / 7.1 (FP16 9.0 / 7.1,
+//     D3Q19 FP16 10.0 / 9.5); not 140k 8.8 / 9.0, 165k tree 9.3 / 10.2, but FP16 9.5 / 9.1
+//     and 178k 9.6 / 9.2, not 185k tree 9.6 / 10.5; not D3Q19 122k tree 9.6 / 9.8, nor FP16
+//     160k 10.8 / 12.1
+//   2 steps, 8 tiles where all groups then run at once (two per compute unit): the time
+//     hardly depends on how many there are, so only near the most: 200k aneurysm 9.0 / 8.5
+//     (FP16 8.8 / 6.5, D3Q19 FP16 9.8 / 8.9), 206k tree 14.4 / 10.9 (a pipe 9.7 / 10.5), not
+//     160k 9.2 / 9.7, 185k tree 9.4 / 11.1, 230k tree 10.1 / 13.4; never D3Q19 FP32, 200k
+//     aneurysm 10.4 / 12.2
+//   interpolated walls: 13k 7.4 / 5.4, 53k 8.0 / 7.1 (D3Q19 9.1 / 8.0), 75k 8.7 / 8.0, not
+//     D3Q19 75k 9.8 / 10.0
 void choose_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, HostPlan& P) {
     const int64_t n = d->n_sites;
     const bool narrow = d->storage != HEMELB_STORE_F32;  // rows of LDS hold twice the sites
@@ -1202,18 +1202,17 @@ void choose_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, H
         return;
     }
     const bool q15 = d->lattice == 15;
-    const int64_t most = d->wall_q ? (q15 ? 80000 : 1 << 16)
-                         : q15     ? (narrow ? 15 << 14 : 27 << 13)
-                                   : (narrow ? 13 << 14 : 1 << 17);
-    if (n > most) return;
+    const int64_t four = d->wall_q ? (q15 ? 80000 : 1 << 16)
+                         : q15     ? (narrow ? 11 << 14 : 1 << 17)
+                                   : (narrow ? 1 << 17 : 7 << 14);
+    const int64_t eight = d->wall_q ? 0 : q15 ? 27 << 13 : narrow ? 13 << 14 : 0;
     constexpr int64_t all = 1 << 30;
     if (n <= 16384 && build_fuse(d, gbase, 3, 1, 512, 1, all, P)) return;
-    if (n <= 80000 && build_fuse(d, gbase, 2, 2, 512, 0, all, P)) return;
-    if (n > (q15 ? 21 << 13 : 1 << 17)) {
-        if (build_fuse(d, gbase, 2, 8, 1024, narrow ? 0 : 2, 512, P)) return;
-        if (!q15 || !narrow) return;
-    }
-    build_fuse(d, gbase, 2, 4, 768, narrow ? 0 : 1, all, P);
+    if (n <= 80000 && n <= four && build_fuse(d, gbase, 2, 2, 512, 0, all, P)) return;
+    if (n <= four)
+        build_fuse(d, gbase, 2, 4, 768, narrow ? 0 : 1, all, P);
+    else if (n > 12 << 14 && n <= eight)
+        build_fuse(d, gbase, 2, 8, 1024, narrow ? 0 : 2, 512, P);
 }
 
 // Validate d and build the host side of its layout (no device work).

@@ -59,6 +59,7 @@ def _pipe(radius, length):
 GEOMS = {
     "pipe13k": wl.pipe,
     "pipe75k": lambda: _pipe(16.0, 94),
+    "pipe140k": lambda: _pipe(19.0, 123),
     "aneurysm_half": lambda: wl.aneurysm(half=True),
     "tree230k": lambda: wl.tree(170, 21.5, (85.0, 85.0, 10.75), 6, seed=5),
     "pipe255k": lambda: _pipe(23.0, 154),
@@ -77,7 +78,10 @@ GEOMS = {
     ("aneurysm_half", 19, "f32", False, False),
     ("aneurysm_half", 19, "f16", False, True),
     ("tree230k", 15, "f32", False, False),
-    ("tree230k", 15, "f16", False, True),
+    ("pipe140k", 15, "f32", False, False),
+    ("pipe140k", 15, "f16", False, True),
+    ("pipe140k", 19, "f16", False, False),
+    ("tree230k", 15, "f16", False, False),
     ("tree230k", 19, "f16", False, False),
     ("pipe255k", 15, "f32", False, False),
     ("pipe255k", 15, "bf16", False, False),
