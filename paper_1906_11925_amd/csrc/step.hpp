@@ -38,29 +38,21 @@ __device__ inline void st_pop(T* p, T v) {
 }
 
 // Incoming population of an iolet link (direction i; its iolet's kind and value v, the
-// link's coefficient) of a site whose stored populations decode to vs and have velocity u
-// (the definition the ghost-fill kernel applies).  Both the step kernel's epilogue and the
-// ghost-fill kernel inline it; without contraction every product and sum rounds on its own
-// in both, so a state restored from a checkpoint gets the same ghost values, bit for bit,
-// as the step that produced it (the moment sums multiply only by 0 and +-1, which is exact
-// either way).
+// link's coefficient) of a site whose stored populations decode to vs (the definition the
+// ghost-fill kernel applies).  Both the step kernel's epilogue and the ghost-fill kernel
+// inline it; without contraction every product and sum rounds on its own in both, so a
+// state restored from a checkpoint gets the same ghost values, bit for bit, as the step that
+// produced it (the moment sums it calls multiply only by 0 and +-1, which is exact either
+// way).
 template <int Q>
-__device__ inline void ghost_velocity(const float (&vs)[Q], float (&u)[3]) {
-#pragma clang fp contract(off)
-    float drho, mx, my, mz;
-    moments<Q>(vs, drho, mx, my, mz);
-    const float ir = 1.0f / (1.0f + drho);
-    u[0] = mx * ir;
-    u[1] = my * ir;
-    u[2] = mz * ir;
-}
-template <int Q>
-__device__ inline float ghost_value(int kind, double v, float coef, int i, const float (&vs)[Q],
-                                    const float (&u)[3]) {
+__device__ inline float ghost_value(int kind, double v, float coef, int i, const float (&vs)[Q]) {
 #pragma clang fp contract(off)
     using Lt = Lat<Q>;
     if (kind == 0) {
-        const float ux = u[0], uy = u[1], uz = u[2];
+        float drho, mx, my, mz;
+        moments<Q>(vs, drho, mx, my, mz);
+        const float ir = 1.0f / (1.0f + drho);
+        const float ux = mx * ir, uy = my * ir, uz = mz * ir;
         const float cu = (float)Lt::cx[i] * ux + (float)Lt::cy[i] * uy + (float)Lt::cz[i] * uz;
         const float usq = ux * ux + uy * uy + uz * uz;
         const float rk = (float)v, rk1 = (float)(v - 1.0);
@@ -68,15 +60,14 @@ __device__ inline float ghost_value(int kind, double v, float coef, int i, const
     }
     return vs[opp(i)] + coef * (float)v;
 }
-// the same for iolet link l at time t
+// the same for iolet link l at time t; a velocity iolet's coefficient alone is loaded
 template <int Q>
 __device__ inline float ghost_value(const Ghosts& G, int64_t l, int i, const float (&vs)[Q],
                                     int64_t t) {
     const int k = G.iolet[l];
-    float u[3];
-    ghost_velocity<Q>(vs, u);
-    return ghost_value<Q>(G.iolets[k].kind, G.vals[(t - G.vals_t0) * G.n_iolets + k], G.coef[l], i,
-                          vs, u);
+    const double v = G.vals[(t - G.vals_t0) * G.n_iolets + k];
+    const int kind = G.iolets[k].kind;
+    return ghost_value<Q>(kind, v, kind == 0 ? 0.f : G.coef[l], i, vs);
 }
 
 // With HLB_FUSE_GHOSTS, a site that owns iolet links also writes the incoming
@@ -199,8 +190,6 @@ __device__ inline void site_collide_store(typename Store<ST>::T* __restrict__ ds
         const int k0 = G.iolet[P.gl];
         const int kind0 = G.iolets[k0].kind;
         const double val0 = G.vals[at + k0];
-        float u[3];
-        ghost_velocity<Q>(vs, u);
         int64_t l = P.gl;
 #pragma unroll
         for (int i0 = 1; i0 < Q; i0 += kLinkBatch) {
@@ -221,7 +210,7 @@ __device__ inline void site_collide_store(typename Store<ST>::T* __restrict__ ds
                     const int k = kio[i - i0];
                     const float v = ghost_value<Q>(k == k0 ? kind0 : G.iolets[k].kind,
                                                    k == k0 ? val0 : G.vals[at + k], coef[i - i0], i,
-                                                   vs, u);
+                                                   vs);
                     dst[tix<Q>(i, slot[i - i0])] = C::enc(i, v);
                 }
         }
