@@ -247,13 +247,14 @@ __global__ __launch_bounds__(kRayTile* kRayTile) void k_render(RenderVolume V, R
 
 // One axis of the distance map: out = min over cells t away on the axis of max(|t|, in),
 // |t| < kFar, else kFar.  FIRST: in is 0 at an occupied cell (grid >= 0 or near != 0), kFar
-// elsewhere.
+// elsewhere.  Rows of workgroups: a map may have more cells than a launch takes threads along
+// one dimension (2^32 - 1).
 template <bool FIRST>
 __global__ __launch_bounds__(kBlock) void k_far(const int32_t* __restrict__ grid,
                                                 const uint8_t* __restrict__ in, int64_t cells,
                                                 int64_t stride, int32_t dim,
                                                 uint8_t* __restrict__ out) {
-    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t c = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kBlock + threadIdx.x;
     if (c >= cells) return;
     const int32_t x = (int32_t)((c / stride) % dim);
     int best = kFar;
@@ -277,7 +278,8 @@ hipError_t launch_render_far(const int32_t* grid, const uint8_t* near, const int
                              uint8_t* tmp, uint8_t* out, hipStream_t s) {
     const int64_t cells = (int64_t)dim[0] * dim[1] * dim[2];
     if (cells == 0) return hipSuccess;
-    const unsigned nb = (unsigned)((cells + kBlock - 1) / kBlock);
+    const int64_t rows = ((cells - 1) / kBlock >> 23) + 1;
+    const dim3 nb((unsigned)(((cells - 1) / kBlock + rows) / rows), (unsigned)rows);
     k_far<true><<<nb, kBlock, 0, s>>>(grid, near, cells, 1, dim[2], out);
     k_far<false><<<nb, kBlock, 0, s>>>(nullptr, out, cells, dim[2], dim[1], tmp);
     k_far<false><<<nb, kBlock, 0, s>>>(nullptr, tmp, cells, (int64_t)dim[1] * dim[2], dim[0], out);

@@ -49,6 +49,9 @@ struct Dim3 {
 static Dim3 g_grid, g_block;
 static size_t g_shared;
 static void* g_stream;
+static uint64_t g_threads;  // of the last launch
+
+uint64_t stand_in_threads() { return g_threads; }
 
 void** __hipRegisterFatBinary(const void*) {
     static void* handle;
@@ -68,7 +71,11 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* shared, void** st
     *grid = g_grid, *block = g_block, *shared = g_shared, *stream = g_stream;
     return 0;
 }
-int hipLaunchKernel(const void* stub, Dim3, Dim3, void**, size_t, void* stream) {
+int hipLaunchKernel(const void* stub, Dim3 grid, Dim3 block, void**, size_t, void* stream) {
+    // threads along a dimension, and workgroups along y and z
+    if ((uint64_t)grid.x * block.x >> 32 || grid.y > 65535 || grid.z > 65535)
+        return g_error = 9;  // hipErrorInvalidConfiguration
+    g_threads = (uint64_t)grid.x * block.x * grid.y * block.y * grid.z * block.z;
     const std::string name = g_kernel.count(stub) ? g_kernel[stub] : "?";
     event("launch " + name, stream);
     if (g_then && name.find(g_watch) != std::string::npos && --g_watch_at == 0) g_then();

@@ -184,3 +184,20 @@ def test_cancel_between_launches_of_several_steps(stand_in, form, after):
         assert lib.hemelb_lb_step(h, 1) == L.HEMELB_ECANCELLED
         assert not launches("k_stream_collide")
     """, HEMELB_FUSE=form)
+
+
+@pytest.mark.parametrize("dim", [(1, 1, 1), (1, 1, 257), (2, 4097, (1 << 19) + 1),
+                                 (1291, 1291, 1291), (1, 1, (1 << 31) - 1), (2, 2, (1 << 31) - 1)])
+def test_distance_maps_of_more_cells_than_one_launch_dimension_takes(stand_in, dim):
+    """A flat vessel's map may pass 2^32 cells (a bounding box may have 2^31 blocks, the map
+    of reach one more along each axis); every cell gets a thread of each of the three passes."""
+    out = _run(stand_in, f"""
+        hip.stand_in_threads.restype = ctypes.c_uint64
+        far = lib._ZN3hlb17launch_render_farEPKiPKhRA3_S0_PhS6_P12ihipStream_t
+        null = ctypes.c_void_p(None)
+        assert far(null, null, (ctypes.c_int32 * 3){dim}, null, null, null) == 0
+        cells = {dim[0]} * {dim[1]} * {dim[2]}
+        assert len(launches("k_far")) == 3
+        assert cells <= hip.stand_in_threads() < cells + cells // 1024 + 256 + 256 * 1024
+    """)
+    assert out == ""
