@@ -1037,13 +1037,13 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
     run_tasks(nt, [&](unsigned w) {
         Part& p = part[w];
         std::vector<int32_t> site;
-        std::vector<uint8_t> seen(n, 0);
+        std::vector<uint8_t> seen(n, 0);  // by the caller's index, as nbr has it
         int32_t count[hlb::kFuseMaxSteps + 1];
         // the sites of R_0 .. R_steps of the tiles [a, b)
         auto grow = [&](int64_t a, int64_t b) {
             site.clear();
             for (int64_t m = a * hlb::kTile; m < std::min(n, b * hlb::kTile); ++m) {
-                seen[m] = 1;
+                seen[P.order[m]] = 1;
                 site.push_back((int32_t)m);
             }
             count[0] = (int32_t)site.size();
@@ -1054,8 +1054,8 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
                     const int64_t s = P.order[site[x]];
                     for (int i = 1; i < q; ++i) {
                         const int32_t v = d->nbr[s * q + i];
-                        if (v < 0 || seen[P.inv[v]]) continue;
-                        seen[P.inv[v]] = 1;
+                        if (v < 0 || seen[v]) continue;
+                        seen[v] = 1;
                         site.push_back(P.inv[v]);
                     }
                 }
@@ -1063,7 +1063,7 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
                 from = to;
                 count[k] = (int32_t)site.size();
             }
-            for (int32_t m : site) seen[m] = 0;
+            for (int32_t m : site) seen[P.order[m]] = 0;
             // a row's codes count to the last local number in 16 bits; the steps between the
             // first and the last hold one site per thread
             const int64_t all = count[steps];
@@ -1123,7 +1123,7 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
     P.fuse_rows.assign(row0[nt] * 4, 0u);
     run_tasks(nt, [&](unsigned w) {
         Part& p = part[w];
-        std::vector<int32_t> local(n, -1);
+        std::vector<int32_t> local(n, -1);  // by the caller's index
         for (size_t k = 0; k < p.site.size(); ++k) {
             const int64_t m = p.site[k];
             P.fuse_list[list0[w] + k] =
@@ -1133,7 +1133,7 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
             const int32_t* site = p.site.data() + p.hdr[h + 1];
             const int32_t nrow = p.hdr[h + 4 + steps - 1], all = p.hdr[h + 4 + steps];
             const int32_t gap = p.hdr[h + 3] = all > pitch ? pitch : 0;
-            for (int32_t x = 0; x < all; ++x) local[site[x]] = x < nrow ? x : x + gap;
+            for (int32_t x = 0; x < all; ++x) local[P.order[site[x]]] = x < nrow ? x : x + gap;
             const size_t base = (row0[w] + (size_t)p.hdr[h + 2]) * 4;
             for (int32_t x = 0; x < nrow; ++x) {
                 const int64_t m = site[x], s = P.order[m];
@@ -1142,7 +1142,7 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
                     const int32_t v = d->nbr[s * q + i];
                     int32_t at = pitch + x;
                     if (v >= 0)
-                        at = pitch + local[P.inv[v]];
+                        at = pitch + local[v];
                     else if (v == HEMELB_LINK_WALL)
                         at = pitch + x + (opp_dir(i) - i) * pitch;
                     else
@@ -1159,7 +1159,6 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
                 for (int c = 0; c < words; ++c)
                     P.fuse_rows[base + ((size_t)(c / 4) * nrow + x) * 4 + c % 4] = row[c];
             }
-            for (int32_t x = 0; x < all; ++x) local[site[x]] = -1;
             p.hdr[h + 1] += (int32_t)list0[w];
             p.hdr[h + 2] += (int32_t)row0[w];
         }
