@@ -1496,24 +1496,22 @@ int64_t planned_device_bytes(const HostPlan& P, int q, size_t elem) {
 int render_distances(hemelb_lb_t h, const std::vector<uint8_t>& near) {
     const int32_t ext[3] = {h->r_gdim[0] + 1, h->r_gdim[1] + 1, h->r_gdim[2] + 1};
     const size_t cells = (size_t)h->r_gdim[0] * h->r_gdim[1] * h->r_gdim[2];
-    uint8_t *flags = nullptr, *tmp = nullptr;
-    int rc = dev_upload(h, &flags, near, "render reach map");
-    if (!rc) rc = dev_alloc(h, &tmp, near.size(), "render reach map");
+    uint8_t* tmp = nullptr;  // the flags, which the first pass alone reads, then scratch
+    int rc = dev_upload(h, &tmp, near, "render reach map");
     if (!rc) rc = dev_alloc(h, &h->r_near, near.size(), "render reach map");
     if (!rc) rc = dev_alloc(h, &h->r_far, cells, "render distance map");
     hipError_t e = hipSuccess;
     if (!rc) {
-        e = hlb::launch_render_far(nullptr, flags, ext, tmp, h->r_near, h->stream);
+        e = hlb::launch_render_far(nullptr, tmp, ext, tmp, h->r_near, h->stream);
         if (e == hipSuccess)
             e = hlb::launch_render_far(h->r_grid, nullptr, h->r_gdim, tmp, h->r_far, h->stream);
         const hipError_t done = hipStreamSynchronize(h->stream);  // before the flags are freed
         if (e == hipSuccess) e = done;
     }
-    for (uint8_t* p : {flags, tmp})
-        if (p) {
-            (void)hipFree(p);
-            h->device_bytes -= (int64_t)near.size();
-        }
+    if (tmp) {
+        (void)hipFree(tmp);
+        h->device_bytes -= (int64_t)near.size();
+    }
     if (!rc && e != hipSuccess) return hip_fail(e, "render distance map");
     return rc;
 }

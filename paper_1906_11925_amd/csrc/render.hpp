@@ -42,7 +42,7 @@ hipError_t launch_render(const RenderVolume& V, const RenderView& v, const float
                          hipStream_t s);
 
 // Distance map of dim[0] x dim[1] x dim[2] cells into out: from each to the nearest with
-// grid >= 0, or near != 0 where grid is null.  tmp: as many bytes.
+// grid >= 0, or near != 0 where grid is null.  tmp: as many bytes, near itself if need be.
 #ifdef HLB_NO_DEVICE  // host-only builds of the planner: no kernels to launch
 inline hipError_t launch_render_far(const int32_t*, const uint8_t*, const int32_t (&)[3], uint8_t*,
                                     uint8_t*, hipStream_t) {
