@@ -1038,8 +1038,9 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
         Part& p = part[w];
         std::vector<int32_t> site;
         std::vector<uint8_t> seen(n, 0);  // by the caller's index, as nbr has it
-        int32_t count[hlb::kFuseMaxSteps + 1];
-        // the sites of R_0 .. R_steps of the tiles [a, b)
+        int32_t count[hlb::kFuseMaxSteps + 1] = {};
+        // the sites of R_0 .. R_steps of the tiles [a, b); whether they fit, which nearly
+        // half the tries do not: those end at the first set that is too large
         auto grow = [&](int64_t a, int64_t b) {
             site.clear();
             for (int64_t m = a * hlb::kTile; m < std::min(n, b * hlb::kTile); ++m) {
@@ -1048,7 +1049,8 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
             }
             count[0] = (int32_t)site.size();
             size_t from = 0;
-            for (int k = 1; k <= steps; ++k) {
+            bool fits = true;
+            for (int k = 1; k <= steps && fits; ++k) {
                 const size_t to = site.size();
                 for (size_t x = from; x < to; ++x) {
                     const int64_t s = P.order[site[x]];
@@ -1059,17 +1061,17 @@ bool build_fuse(const hemelb_lb_desc_t* d, const std::vector<int64_t>& gbase, in
                         site.push_back(P.inv[v]);
                     }
                 }
-                std::sort(site.begin() + to, site.end());  // neighbouring sites in neighbouring lanes
+                // a row of LDS holds the sets before the last; the steps between the first and
+                // the last hold one site per thread; and a row's codes count to the last local
+                // number in 16 bits
+                const int64_t all = count[k] = (int32_t)site.size();
+                fits = k == steps ? (pitch + all + (all > pitch ? pitch : 0)) * elem <= 1 << 16
+                                  : all <= pitch && (k == steps - 1 || all <= threads);
+                if (fits) std::sort(site.begin() + to, site.end());  // neighbours in neighbouring lanes
                 from = to;
-                count[k] = (int32_t)site.size();
             }
             for (int32_t m : site) seen[P.order[m]] = 0;
-            // a row's codes count to the last local number in 16 bits; the steps between the
-            // first and the last hold one site per thread
-            const int64_t all = count[steps];
-            return count[steps - 1] <= pitch &&
-                   (pitch + all + (all > pitch ? pitch : 0)) * elem <= 1 << 16 &&
-                   (steps == 2 || count[steps - 2] <= threads);
+            return fits;
         };
         const int64_t end = ttiles * (w + 1) / nt;
         for (int64_t T = ttiles * w / nt; T < end && p.fits;) {
